@@ -21,8 +21,8 @@
  *     (FL_F32: float; FL_BF16: bfloat16 storage, fp32 accumulation and fp32
  *     softmax / LayerNorm statistics).  Device pointers must be 16-byte aligned.
  *   - `hip_stream` is the caller's hipStream_t (0 = the null stream).  All work
- *     is ordered on it: kernels are enqueued there or on library-owned streams
- *     that wait for it and that it waits for (see fl_set_grad_overlap), so work
+ *     is ordered on it: kernels are enqueued there or on a library-owned stream
+ *     that waits for it and that it waits for (see fl_set_grad_overlap), so work
  *     the caller enqueues afterwards sees every result.  forward/backward never
  *     synchronise the device.
  *   - Every call returns fl_status_t; no exception or abort crosses this ABI.
@@ -165,39 +165,27 @@ fl_status_t fl_layer_destroy(fl_layer_t *layer);
 /* Thread-local text of the last error returned on this thread ("" if none). */
 const char *fl_last_error(void);
 
-/* Backward passes started after this call do (non-zero, the default) or do not (0) run the
- * parameter-gradient kernels -- bias sums, the dW contractions and the second stages of their
- * reductions -- on a library-owned side stream beside the input-gradient chain (Section 4.1.3: the
- * backward pass is a reverse replay of the recorded graph; kernels of independent branches of that
- * graph may run at the same time).  The side stream waits, through events, for the gradients it
- * reads, and the caller's stream waits for it before fl_layer_backward returns control of dX and
- * the gradient buffers to work enqueued later on that stream: the caller sees the same ordering
- * either way, and the results are bit-identical.  Small problems (B*T*d_model < 2^18) always stay on
- * one stream.  The same switch decides where forward writes the transposed weight copies it leaves for
- * its backward (bf16 layers of middling size): on the side stream, or in order on the caller's.
- * Process-wide; a call that is already inside forward or backward when the switch changes may see
- * either setting for its remaining operators (both are correct).
+/* Forward passes started after this call write the transposed weight copies that they leave for their backward
+ * (bf16 layers of middling size) on a library-owned side stream beside the forward pass (non-zero, the default), or
+ * in order on the caller's stream (0).  The side stream waits, through an event, for the parameters, and the caller's
+ * stream waits for it before the first kernel that reads a copy: the results are bit-identical.  Everything else
+ * runs on the caller's stream.  (The name is older: the parameter gradients used to run there, beside the
+ * input-gradient chain; one launch for all of them at the end of the pass is faster.)
+ * Process-wide; a call that is already inside forward when the switch changes may see either setting.
  *
  * Graph capture: once calls with the same sizes have warmed the allocator's cache (so that no device
  * allocation happens), fl_layer_forward + fl_layer_backward on a capturing stream record a valid
- * graph -- the side streams enter the capture through the fork events and leave it at the join --
- * and replays reproduce the eager results bit for bit.  Timing (fl_prof_enable) must be off. */
+ * graph -- the side stream enters the capture through the fork event and leaves it where the copies are first
+ * read -- and replays reproduce the eager results bit for bit.  Timing (fl_prof_enable) must be off. */
 fl_status_t fl_set_grad_overlap(int32_t enabled);
 
-/* Deferred join, for stacks of layers (Section 4.2: a model is a sequence of modules whose backward
- * passes run one after the other).  With it enabled (non-zero; default 0) fl_layer_backward no longer
- * makes the caller's stream wait for the side stream before it returns: dX is complete in stream order
- * as always (the input-gradient chain never leaves the caller's stream), so the backward pass of the
- * layer below can start while this layer's last parameter-gradient kernels still run, but the buffers
- * in `grads` are complete only after fl_layer_join(layer, stream), which makes `stream` (and the stream
- * the layer ran on) wait for them.  The next fl_layer_forward on the handle and fl_layer_destroy join
- * by themselves.  Until the join, the layer keeps the activations its side-stream kernels read, and the
- * caller keeps X unchanged (a post-LN layer's last weight-gradient kernel reads it).  dY is free for reuse
- * in stream order as soon as fl_layer_backward has returned: the caller's stream waits for the side-stream
- * kernels that read it (the first ones of the pass), so a stack may alternate between two gradient buffers.
- * Without a side stream (small problems, fl_set_grad_overlap(0)) nothing is deferred and the join is a
- * no-op.  Results are bit-identical either way.  Do not enable it under graph capture unless the
- * captured region contains the join. */
+/* Joining a stack of layers (Section 4.2: a model is a sequence of modules whose backward passes run one after the
+ * other).  A backward pass runs on the caller's stream and is complete there in stream order.  With the deferred
+ * join enabled (non-zero; default 0) the caller promises to read the buffers in `grads` only after
+ * fl_layer_join(layer, stream), which makes `stream` wait for the layer's last backward pass when it is another
+ * stream than the one that pass ran on.  X stays unchanged until the pass has run (its weight-gradient kernel reads
+ * it); dY is free for reuse in stream order as soon as fl_layer_backward has returned.  Results are bit-identical
+ * either way. */
 fl_status_t fl_layer_set_deferred_join(fl_layer_t *layer, int32_t enabled);
 fl_status_t fl_layer_join(fl_layer_t *layer, void *hip_stream);
 

@@ -47,6 +47,13 @@ void fl_test_gemm_force_variant(int32_t v);
 /* Tile height of the plain GEMM kernel: 0 automatic, 1 = 64x128 tiles, 2 = 128x128 tiles. */
 void fl_test_gemm_force_tile_height(int32_t tmw);
 
+/* The launch that ends a backward pass, with two weight gradients and one bias sum: dW[N,K] = gy^T x, dWt[K,N] = x^T gy
+ * over M tokens (gy [M,N], x [M,K]), db[n] = sum_m gy[m,n].  kernel: -1 the library's choice (and its token split;
+ * `splits` is ignored), else 0 256x256, 1 256x128, 2 128x128, 3 64x64, 4 32x32 tiles (fp32: 3 and 4) with `splits` token
+ * ranges; `partial` holds 2*splits*N*K floats (the library's choice never takes more than 16 ranges). */
+int32_t fl_test_dw_batch(int32_t dtype, int32_t kernel, int32_t splits, int32_t accumulate, const void *gy, const void *x,
+                         int32_t M, int32_t N, int32_t K, void *dW, void *dWt, void *db, float *partial, void *hip_stream);
+
 /* LayerNorm (a normalisation primitive, Section 4.2) over the last dimension of x[M,D]. */
 int32_t fl_test_layernorm_fwd(int32_t dtype, const void *x, const void *gamma, const void *beta, float eps, int32_t M,
                               int32_t D, void *y, float *mean, float *rstd, void *hip_stream);

@@ -57,6 +57,7 @@ void gemm_pipe_force_variant(int v);
 void gemm_force_tile_height(int tmw);
 void attention_force_general(bool on);
 void attention_force_unfused_bwd(bool on);
+void dw_force_kernel(int k);
 #endif
 
 // fp32 outputs with few tiles (gemm_f32_small.hip): 32 x 32 tiles, the four wavefronts of a workgroup
@@ -64,10 +65,39 @@ void attention_force_unfused_bwd(bool on);
 bool gemm_f32_small_applies(int M, int N);
 hipError_t launch_gemm_f32_small(const GemmArgs &a, const void *gemm_dev, int splits, hipStream_t s);
 
+hipError_t launch_gemm_small(int dt, const GemmArgs &a, const void *gemm_dev, int splits, int variant, hipStream_t s);
+
 // The pipelined bf16 kernel (gemm_pipe.hip); launch_gemm uses it whenever the problem is eligible.
 bool gemm_pipe_eligible(const GemmArgs &a, int k_per_split);
 int gemm_pipe_pick_variant(bool a_kc, bool b_kc, int M, int N, int K, bool alone = false);  // < 0: use the kernel in gemm.hip
 hipError_t launch_gemm_bf16_pipe(const GemmArgs &a, const void *gemm_dev, int splits, int variant, hipStream_t s);
+
+// ---------------------------------------------------------------------------
+// All parameter gradients of one backward pass that are sums over its M tokens, in one launch (gemm_dw.h):
+// jobs[j].out[N, K] = sum_m gy[m, n] x[m, k] (row-major, leading dimensions N and K), and column sums
+// out[n] = sum_r in[r * ld + n] over `rows` rows of bf16 or fp32 (f32: always with dt fp32, and for fp32 partial rows).  accumulate: added to what
+// `out` holds.  With plan.splits > 1 the fp32 partial sums of job j go to jobs[j].partial ([splits][N*K] floats)
+// instead of `out`, and the caller adds them up (launch_reduce_batch).
+constexpr int DW_MAX_JOBS = 4, DW_MAX_COLS = 10;
+struct DwJob {
+  const void *gy, *x;
+  void *out;
+  float *partial;
+  int N, K;
+};
+struct ColJob {
+  const void *in;
+  void *out;
+  int rows, ld, n, f32;
+};
+enum { DW_256 = 0, DW_256x128 = 1, DW_128 = 2, DW_SMALL64 = 3, DW_SMALL32 = 4 };
+struct DwPlan { int kernel, splits; };
+DwPlan dw_plan(int dt, const DwJob *jobs, int njobs, int M);   // the kernel and token split for these problems
+hipError_t launch_dw_batch(int dt, const DwPlan &plan, const DwJob *jobs, int njobs, const ColJob *cols, int ncols, int M,
+                           bool accumulate, hipStream_t stream);
+hipError_t launch_dw_small(int dt, int tile, const DwJob *jobs, int njobs, const ColJob *cols, int ncols, int M, int splits,
+                           bool accumulate, hipStream_t stream);
+int forced_dw_kernel();   // -1 = automatic
 
 // out_s[n] = sum_p partial[p*stride + s*seglen + n]  for s < nseg (<= 3), n < seglen;
 // out_s has element type dt.  seglen % 4 == 0.

@@ -147,45 +147,21 @@ struct fl_layer {
   uint64_t rec_seed = 0;
   // valid during backward
   bool accumulate = false;  // parameter gradients are added to what the caller's buffers hold
-  // Parameter-gradient work (bias sums, dW GEMMs, second-stage reductions) is enqueued on a side
-  // stream so that it runs beside the input-gradient chain; see side_mark(), side_begin(), side_join().
-  hipStream_t side = nullptr;          // non-null while this backward uses the side stream
-  std::vector<hipEvent_t> fork_events; // one per fork, reused by the next backward
-  size_t forks = 0;
+  // Parameter gradients that are sums over the tokens (weight gradients, bias sums, the second stage of the LayerNorm
+  // sums): collected while the tape is replayed and run as one launch at its end (dw_flush), with the buffers they
+  // read held until then.
+  DwJob dw_jobs[DW_MAX_JOBS];
+  ColJob dw_cols[DW_MAX_COLS];
+  int n_dw_jobs = 0, n_dw_cols = 0;
+  std::vector<Buf *> held;
+  bool defer_join = false;             // fl_layer_join orders another stream behind the last backward pass
+  bool join_open = false;              // a backward pass with defer_join has ended and nobody has joined since
   hipEvent_t join_event = nullptr;
-  hipEvent_t attn_join_event = nullptr;  // dK/dV kernels on the second side stream -> layer's stream
-  std::vector<Buf *> held;             // buffers the side stream reads: released after the join
-  bool defer_join = false;             // backward leaves the join to fl_layer_join() / the next call on the layer
-  bool join_pending = false;           // a backward has ended without the join: join_event marks its side-stream work
-  // Deferred join: side-stream kernels that read the CALLER's dY.  The layer's stream waits for them before
-  // backward returns (they are the first parameter-gradient kernels of the pass and long done by then), so
-  // that the caller may reuse dY's memory in stream order as soon as backward has returned.
-  hipEvent_t caller_read_event = nullptr;
-  bool caller_read_pending = false;
   // Transposed copies of Wqkv, Wo, W1, W2 (in kLinear order), made by forward for the input-gradient
   // GEMMs of its backward; see wt_make(), wt_acquire(), wt_release().
   Buf *wt[4] = {nullptr, nullptr, nullptr, nullptr};
   hipEvent_t wt_fork_event = nullptr, wt_event = nullptr;
   bool wt_on_side = false;             // made on the side stream, and the layer's stream has not waited yet
-  // Second stages of the backward pass's two-stage reductions (split weight gradients, LayerNorm sums, bias
-  // sums): collected while the tape is replayed and run as ONE launch at the end of the parameter-gradient
-  // lane; the partial buffers are kept until then.
-  std::vector<ReduceJob> reduce_jobs;
-  std::vector<Buf *> reduce_bufs;
-  std::vector<char> reduce_job_main;   // per job: its partial sums were written on the layer's stream
-  // The pass's last linear operator (see linear_backward): where the side stream stood when its work began.
-  int tail_node = -1;                  // tape index of that operator; -1 = the pass does not split its tail
-  bool tail_split = false;
-  size_t tail_jobs = 0;                // second stages collected before that point
-  hipEvent_t tail_event = nullptr;     // recorded on the side stream at that point
-  hipStream_t reduce_stream = nullptr;
-  bool reduce_has_side = false;        // some collected job's partial sums were written on the side stream
-  bool reduce_from_main = false;       // some collected job's partial sums were written on the layer's stream
-                                       // after the last fork: the side stream has not been told to wait for them
-  // Every fork puts a barrier on the layer's stream (the recorded event), a few microseconds in which the
-  // input-gradient chain stands still.  The first linear operator replayed therefore does not fork: its
-  // parameter-gradient work waits here for the next operator's fork and runs in front of that one's.
-  std::vector<std::function<int(hipStream_t)>> pending_side;
   bool inference = false;              // forward keeps nothing for a backward pass (no pre-activation copy)
   const void *params[P_COUNT];
   void *grads[P_COUNT];
@@ -341,7 +317,8 @@ struct Scratch {
 };
 
 // ---- side stream ---------------------------------------------------------------------------
-// One stream per process, default priority, never destroyed.  It has no implicit ordering with
+// For the transposed weight copies that forward leaves to its backward (see wt_make): nothing in forward waits for
+// them.  One stream per process, default priority, never destroyed.  It has no implicit ordering with
 // any other stream: every dependency is an event.
 std::atomic<bool> g_overlap{true};
 // Events that order this library's streams among themselves on one device: no timing and no
@@ -359,104 +336,6 @@ hipStream_t side_stream() {
   static hipStream_t s = make_side_stream();
   return s;
 }
-// A second one for the dK/dV kernels of the attention backward, which run beside the dQ kernel: on the
-// first side stream they would queue up behind the weight-gradient GEMMs.
-hipStream_t side_stream2() {
-  static hipStream_t s = make_side_stream();
-  return s;
-}
-// Fork in two steps, so that the host can enqueue the next kernel of the critical path on the layer's
-// stream BETWEEN them (enqueueing costs the host a few microseconds per call, and the GPU would wait):
-// side_mark() records "everything enqueued on the layer's stream so far" in an event; side_begin()
-// makes the side stream wait for that point and returns the stream to launch the parameter-gradient
-// kernels on (the layer's own stream when overlap is off).
-int side_mark(fl_layer *L, hipEvent_t *ev) {
-  *ev = nullptr;
-  if (!L->side) return 0;
-  if (L->forks == L->fork_events.size()) {
-    hipEvent_t e = nullptr;
-    FL_HIP(hipEventCreateWithFlags(&e, kEventFlags));
-    L->fork_events.push_back(e);
-  }
-  *ev = L->fork_events[L->forks++];
-  FL_HIP(hipEventRecord(*ev, L->stream));
-  return 0;
-}
-int side_begin(fl_layer *L, hipEvent_t ev, hipStream_t *out) {
-  *out = L->stream;
-  if (!L->side) return 0;
-  FL_HIP(hipStreamWaitEvent(L->side, ev, 0));
-  *out = L->side;
-  L->reduce_from_main = false;  // whatever the layer's stream wrote before the event is ordered now
-  return 0;
-}
-// A buffer that kernels on the side stream read must not go back to the cache of the layer's stream
-// (where later kernels could overwrite it) before the join.
-void side_hold(fl_layer *L, Buf *b) {
-  if (!L->side || !b) return;
-  b->refs++;
-  L->held.push_back(b);
-}
-// The layer's stream waits for the side stream; afterwards the held buffers may be reused.
-// wait_host: on an error path, where the order of what was enqueued is no longer known.
-int side_join(fl_layer *L, bool wait_host, bool defer = false) {
-  int rc = 0;
-  const bool caller_read = L->caller_read_pending;
-  L->caller_read_pending = false;
-  if (defer && !wait_host && L->side && L->forks) {
-    // Only mark the end of this backward's side-stream work; the held buffers stay held until
-    // finish_pending_join().  (A failure to record falls through to the immediate join.)
-    hipError_t e = hipSuccess;
-    if (!L->join_event) e = hipEventCreateWithFlags(&L->join_event, kEventFlags);
-    if (e == hipSuccess) e = hipEventRecord(L->join_event, L->side);
-    if (e == hipSuccess && caller_read) e = hipStreamWaitEvent(L->stream, L->caller_read_event, 0);
-    if (e == hipSuccess) {
-      L->join_pending = true;
-      L->forks = 0;
-      L->side = nullptr;
-      return 0;
-    }
-  }
-  if (L->side && L->forks) {
-    if (wait_host) {
-      hipStreamSynchronize(L->side);
-    } else {
-      hipError_t e = hipSuccess;
-      if (!L->join_event) e = hipEventCreateWithFlags(&L->join_event, kEventFlags);
-      if (e == hipSuccess) e = hipEventRecord(L->join_event, L->side);
-      if (e == hipSuccess) e = hipStreamWaitEvent(L->stream, L->join_event, 0);
-      if (e != hipSuccess) {
-        hipStreamSynchronize(L->side);
-        rc = set_error(FL_ERR_DEVICE, "joining the side stream failed: %s", hipGetErrorString(e));
-      }
-    }
-  }
-  for (Buf *&b : L->held) buf_unref(b);
-  L->held.clear();
-  L->forks = 0;
-  L->side = nullptr;
-  return rc;
-}
-
-// Completes a join that backward left open: the layer's stream (whose cache the held buffers return to)
-// waits for the marked point of the side stream, and so does `also` when it is another stream.  Where a
-// stream cannot wait (wait_host: destroy and error paths; or the caller has destroyed the stream since),
-// the host waits instead, as wt_release() does.
-int finish_pending_join(fl_layer *L, hipStream_t also, bool wait_host) {
-  if (L->join_pending) {
-    bool ordered = !wait_host && hipStreamWaitEvent(L->stream, L->join_event, 0) == hipSuccess &&
-                   (also == L->stream || hipStreamWaitEvent(also, L->join_event, 0) == hipSuccess);
-    if (!ordered) {
-      (void)hipGetLastError();
-      if (hipEventSynchronize(L->join_event) != hipSuccess) hipStreamSynchronize(side_stream());
-    }
-    L->join_pending = false;
-  }
-  for (Buf *&b : L->held) buf_unref(b);
-  L->held.clear();
-  return 0;
-}
-
 // The transposed weights go back to the cache of the layer's stream: if they were written on the side
 // stream and nobody has waited for that yet, the layer's stream (or, when it may no longer exist, the
 // host) waits first, so that whatever the cache hands the memory to next is ordered after the writes.
@@ -553,103 +432,65 @@ int wt_acquire(fl_layer *L) {
   return 0;
 }
 
-// ---- batched second stages ---------------------------------------------------------------
-// Every job's partial sums are produced on `ps` (or, for the LayerNorm sums, made visible to it by a fork)
-// before anything enqueued later on `ps`: the batch launched at the end of the pass is ordered after them.
-int reduce_flush(fl_layer *L) {
-  int rc = 0;
-  if (!L->reduce_jobs.empty()) {
-    hipStream_t ps = L->reduce_stream;
-    if (L->reduce_from_main && ps != L->stream) {
-      if (!L->reduce_has_side) {
-        ps = L->stream;  // every partial sum was written on the layer's stream: reduce there, in order
-      } else {           // make the side stream wait for what the layer's stream wrote
-        hipEvent_t ev;
-        rc = side_mark(L, &ev);
-        if (!rc) rc = side_begin(L, ev, &ps);
-      }
-    }
-    if (!rc) {
-      double bytes = 0;
-      for (const ReduceJob &j : L->reduce_jobs) bytes += (double)(j.P * 4 + esize(L)) * j.seglen * j.nseg;
-      hipError_t he = timed(FL_K_SPLITK_REDUCE, 0, bytes, ps, [&] {
-        return launch_reduce_batch(L->dt, L->reduce_jobs.data(), (int)L->reduce_jobs.size(), ps, L->accumulate);
-      });
-      if (he != hipSuccess)
-        rc = set_error(FL_ERR_DEVICE, "the batched second-stage reduction failed: %s", hipGetErrorString(he));
-    }
-  }
-  for (Buf *&b : L->reduce_bufs) buf_unref(b);   // back to the cache of the stream that has just read them
-  L->reduce_bufs.clear();
-  L->reduce_jobs.clear();
-  L->reduce_job_main.clear();
-  L->reduce_from_main = false;
-  L->reduce_has_side = false;
-  L->tail_split = false;   // a flush in the middle of the pass: the tail is no longer what was counted
-  return rc;
+// ---- parameter gradients -------------------------------------------------------------------
+// A buffer that the launch at the end of the pass reads must not go back to the cache before it.
+void hold(fl_layer *L, Buf *b) {
+  if (!b) return;
+  b->refs++;
+  L->held.push_back(b);
 }
-// The end of a pass whose last linear operator marked the side stream (tail_split): the second stages
-// collected before the mark, and those whose partial sums the layer's stream wrote itself, run on the
-// LAYER's stream -- which has nothing left to do while the side stream still works on that operator's
-// weight gradient -- and only the rest behind that weight gradient on the side stream.  Same kernel,
-// same summation order: which launch a job is part of does not change its result.
-int reduce_flush_split(fl_layer *L) {
-  std::vector<ReduceJob> on_main, on_side;
-  for (size_t i = 0; i < L->reduce_jobs.size(); ++i)
-    (i < L->tail_jobs || L->reduce_job_main[i] ? on_main : on_side).push_back(L->reduce_jobs[i]);
-  int rc = 0;
-  auto launch = [&](std::vector<ReduceJob> &jobs, hipStream_t ps) {
-    for (size_t at = 0; at < jobs.size() && !rc; at += REDUCE_MAX_JOBS) {
-      const int n = (int)std::min<size_t>(REDUCE_MAX_JOBS, jobs.size() - at);
-      double bytes = 0;
-      for (int k = 0; k < n; ++k) bytes += (double)(jobs[at + k].P * 4 + esize(L)) * jobs[at + k].seglen * jobs[at + k].nseg;
-      hipError_t he = timed(FL_K_SPLITK_REDUCE, 0, bytes, ps,
-                            [&] { return launch_reduce_batch(L->dt, jobs.data() + at, n, ps, L->accumulate); });
-      if (he != hipSuccess)
-        rc = set_error(FL_ERR_DEVICE, "the batched second-stage reduction failed: %s", hipGetErrorString(he));
-    }
-  };
-  if (!on_main.empty()) {
-    hipError_t he = hipStreamWaitEvent(L->stream, L->tail_event, 0);
-    if (he != hipSuccess) rc = set_error(FL_ERR_DEVICE, "waiting for the side stream failed: %s", hipGetErrorString(he));
-    if (!rc) launch(on_main, L->stream);
-  }
-  if (!rc) launch(on_side, L->side);
-  // the partial sums came from either stream's cache and were read on either stream: they go back after the join
-  for (Buf *&b : L->reduce_bufs) L->held.push_back(b);
-  L->reduce_bufs.clear();
-  L->reduce_jobs.clear();
-  L->reduce_job_main.clear();
-  L->reduce_from_main = false;
-  L->reduce_has_side = false;
-  L->tail_split = false;
-  return rc;
+void dw_drop(fl_layer *L) {
+  for (Buf *&b : L->held) buf_unref(b);
+  L->held.clear();
+  L->n_dw_jobs = L->n_dw_cols = 0;
 }
-// ps: the stream the batch will run on (the side stream while there is one).  from_main: the partial sums were
-// written by a kernel on the layer's stream that no fork has covered yet.
-int reduce_later(fl_layer *L, hipStream_t ps, bool from_main, Buf *partial, int P, size_t stride, size_t seglen,
-                 int nseg, void *o0, void *o1, void *o2) {
-  if (!L->reduce_jobs.empty() && (L->reduce_stream != ps || (int)L->reduce_jobs.size() == REDUCE_MAX_JOBS))
-    FL_TRY(reduce_flush(L));
-  L->reduce_stream = ps;
-  if (from_main && ps != L->stream) L->reduce_from_main = true;
-  if (!from_main && ps != L->stream) L->reduce_has_side = true;
-  ReduceJob j;
-  j.partial = static_cast<const float *>(partial->ptr);
-  j.P = P; j.nseg = nseg; j.stride = stride; j.seglen = seglen;
-  j.out[0] = o0; j.out[1] = o1; j.out[2] = o2;
-  L->reduce_jobs.push_back(j);
-  L->reduce_job_main.push_back(from_main ? 1 : 0);
-  partial->refs++;
-  L->reduce_bufs.push_back(partial);
+int dw_column(fl_layer *L, const void *in, int rows, int ld, int n, bool f32, void *out) {
+  if (!out) return 0;
+  if (L->n_dw_cols == DW_MAX_COLS) return set_error(FL_ERR_UNSUPPORTED, "too many column sums in one backward pass");
+  L->dw_cols[L->n_dw_cols++] = ColJob{in, out, rows, ld, n, f32 || L->dt == DT_F32 ? 1 : 0};
   return 0;
 }
-int run_pending_side(fl_layer *L, hipStream_t ps) {
-  int rc = 0;
-  for (auto &f : L->pending_side)
-    if (!rc) rc = f(ps);
-  L->pending_side.clear();
-  return rc;
+// Runs what the pass has collected: one launch, and a second one where the plan cuts the tokens into ranges.
+int dw_flush(fl_layer *L) {
+  struct Drop {
+    fl_layer *L;
+    ~Drop() { dw_drop(L); }
+  } drop{L};
+  const int n = L->n_dw_jobs;
+  if (!n) return 0;
+  OpTag tag(FL_OP_LINEAR_BWD, 0);
+  hipStream_t st = L->stream;
+  const DwPlan plan = dw_plan(L->dt, L->dw_jobs, n, L->M);
+  double fl = 0, by = 0;
+  size_t elems = 0;
+  for (int j = 0; j < n; ++j) {
+    const DwJob &J = L->dw_jobs[j];
+    elems += (size_t)J.N * J.K;
+    fl += 2.0 * L->M * J.N * J.K;
+    by += ((double)L->M * J.N + (double)L->M * J.K + (double)J.N * J.K) * esize(L);
+  }
+  Scratch ws;
+  if (plan.splits > 1) {
+    FL_TRY(ws.get(elems * plan.splits * sizeof(float), st));
+    float *at = ws.f32();
+    for (int j = 0; j < n; ++j) {
+      L->dw_jobs[j].partial = at;
+      at += (size_t)L->dw_jobs[j].N * L->dw_jobs[j].K * plan.splits;
+    }
+  }
+  FL_HIP(timed(FL_K_GEMM_TN, fl, by, st, [&] {
+    return launch_dw_batch(L->dt, plan, L->dw_jobs, n, L->dw_cols, L->n_dw_cols, L->M, L->accumulate, st);
+  }));
+  if (plan.splits > 1) {
+    ReduceJob jobs[DW_MAX_JOBS];
+    for (int j = 0; j < n; ++j) {
+      const size_t len = (size_t)L->dw_jobs[j].N * L->dw_jobs[j].K;
+      jobs[j] = ReduceJob{L->dw_jobs[j].partial, plan.splits, 1, len, len, {L->dw_jobs[j].out, nullptr, nullptr}};
+    }
+    FL_HIP(timed(FL_K_SPLITK_REDUCE, 0, (double)(plan.splits * 4 + esize(L)) * elems, st,
+                 [&] { return launch_reduce_batch(L->dt, jobs, n, st, L->accumulate); }));
+  }
+  return 0;
 }
 
 // ---- gradient functions ---------------------------------------------------------------
@@ -682,14 +523,10 @@ int linear_backward(void *ctx, Tape *tape, const Node *n) {
     }
     gy = gm->ptr;
   }
-  struct Unref {  // gm lives until this function returns (the side stream holds its own reference)
+  struct Unref {  // gm lives until this function returns (the weight gradient holds its own reference)
     Buf *&b;
     ~Unref() { buf_unref(b); }
   } unref_gm{gm};
-  // The first linear operator of the replay leaves its parameter-gradient work to the next fork (see pending_side).
-  const bool defer_side = L->side && L->forks == 0 && L->pending_side.empty() && self > 1;
-  hipEvent_t forked = nullptr;
-  if (!defer_side) FL_TRY(side_mark(L, &forked));   // gy is complete at this point of the layer's stream
   // input gradient: dx[M,K] = gy W (+ what other consumers of x already contributed)
   {
     Slot &xs = tape->slots[n->in0];
@@ -730,86 +567,13 @@ int linear_backward(void *ctx, Tape *tape, const Node *n) {
     set_grad(xs, a.C, nb);
     if (a.dact) xs.xform_done = true;
   }
-  // The parameter gradients need gy and the saved input only and nobody waits for them before the
-  // backward pass ends: they go to the side stream, beside the input-gradient chain (whose GEMM is
-  // already enqueued above).
-  side_hold(L, gm ? gm : ys.grad_buf);
-  side_hold(L, tape->slots[n->in0].value_buf);
-  // The pass's last linear operator: nothing follows its input gradient on the layer's stream, while the
-  // side stream still has this operator's weight gradient and every second stage ahead of it.  So its
-  // bias sums run on the layer's stream behind the input gradient, and the second stages split (see
-  // reduce_flush_split).  Measured on the BERT-base shape: the side stream used to end 45 us after the
-  // layer's stream.
-  const bool tail = L->side && !defer_side && self == L->tail_node;
-  const bool need_colsum = !ys.colsum_done;
-  const bool colsum_here = need_colsum && !tail;
-  const bool reads_callers_dy = L->side && L->defer_join && !gm && !ys.grad_buf;
-  const void *x_saved = n->s0;
-  const int lin = n->param;
-  auto side_work = [=](hipStream_t ps) -> int {
-    OpTag tag2(FL_OP_LINEAR_BWD, self);
-    // bias gradient, unless the kernel that finished gy already produced it: first stage here, second stage
-    // batched with the others
-    if (colsum_here) {
-      Scratch ws;
-      FL_TRY(ws.get(colsum_ws_floats(M, N) * sizeof(float), ps));
-      FL_HIP(timed(FL_K_COLSUM, 0, (double)M * N * e, ps,
-                   [&] { return launch_colsum_stage1(dt, gy, M, N, ws.f32(), ps); }));
-      FL_TRY(reduce_later(L, ps, false, ws.b, colsum_stage1_rows(M), (size_t)N, (size_t)N, 1,
-                          L->grads[kLinear[lin].b], nullptr, nullptr));
-    }
-    // weight gradient: dW[N,K] = sum_m gy[m,n] x[m,k]
-    GemmArgs a;
-    a.A = gy; a.lda = N; a.a_kc = false;
-    a.B = x_saved; a.ldb = K; a.b_kc = false;
-    a.M = N; a.N = K; a.K = M;
-    a.C = L->grads[kLinear[lin].w]; a.ldc = K;
-    a.splits = gemm_pick_splits(dt, a.M, a.N, a.K);
-    const double fl = 2.0 * M * N * K, by = ((double)M * N + (double)M * K + (double)N * K) * e;
-    if (a.splits > 1) {
-      Scratch ws;
-      FL_TRY(ws.get((size_t)a.splits * N * K * sizeof(float), ps));
-      a.partial = ws.f32();
-      FL_HIP(timed(FL_K_GEMM_TN, fl, by, ps, [&] { return launch_gemm(dt, a, ps); }));
-      FL_TRY(reduce_later(L, ps, false, ws.b, a.splits, (size_t)N * K, (size_t)N * K, 1, a.C, nullptr, nullptr));
-    } else {
-      if (L->accumulate) a.residual = a.C;  // in place: each lane reads the elements it then writes
-      FL_HIP(timed(FL_K_GEMM_TN, fl, by, ps, [&] { return launch_gemm(dt, a, ps); }));
-    }
-    if (reads_callers_dy) {  // gy is the caller's dY, and these were its readers
-      if (!L->caller_read_event) FL_HIP(hipEventCreateWithFlags(&L->caller_read_event, kEventFlags));
-      FL_HIP(hipEventRecord(L->caller_read_event, L->side));
-      L->caller_read_pending = true;
-    }
-    return 0;
-  };
-  // The parameter gradients need gy and the saved input only and nobody waits for them before the
-  // backward pass ends: they go to the side stream, beside the input-gradient chain (whose GEMM is
-  // already enqueued above).
-  if (defer_side) {
-    L->pending_side.push_back(side_work);
-  } else {
-    hipStream_t ps;
-    FL_TRY(side_begin(L, forked, &ps));
-    FL_TRY(run_pending_side(L, ps));
-    if (tail) {
-      if (!L->tail_event) FL_HIP(hipEventCreateWithFlags(&L->tail_event, kEventFlags));
-      FL_HIP(hipEventRecord(L->tail_event, ps));
-      L->tail_jobs = L->reduce_jobs.size();
-      L->tail_split = true;
-      if (need_colsum) {   // on the layer's stream, behind the input gradient enqueued above
-        Scratch ws;
-        FL_TRY(ws.get(colsum_ws_floats(M, N) * sizeof(float), st));
-        FL_HIP(timed(FL_K_COLSUM, 0, (double)M * N * e, st,
-                     [&] { return launch_colsum_stage1(dt, gy, M, N, ws.f32(), st); }));
-        FL_TRY(reduce_later(L, ps, true, ws.b, colsum_stage1_rows(M), (size_t)N, (size_t)N, 1,
-                            L->grads[kLinear[lin].b], nullptr, nullptr));
-      }
-    }
-    FL_TRY(side_work(ps));
-    // (the second stages stay collected until the end of the pass: one launch there measured better than a
-    // launch after every operator, 0.408 against 0.413 ms per step on the BERT-base shape)
-  }
+  // The parameter gradients need gy and the saved input only and nobody waits for them before the backward pass ends:
+  // dW[N,K] = sum_m gy[m,n] x[m,k], and db unless the kernel that finished gy already summed its columns.
+  if (L->n_dw_jobs == DW_MAX_JOBS) return set_error(FL_ERR_UNSUPPORTED, "too many linear operators in one backward pass");
+  L->dw_jobs[L->n_dw_jobs++] = DwJob{gy, n->s0, L->grads[kLinear[n->param].w], nullptr, N, K};
+  if (!ys.colsum_done) FL_TRY(dw_column(L, gy, M, N, N, false, L->grads[kLinear[n->param].b]));
+  hold(L, gm ? gm : ys.grad_buf);
+  hold(L, tape->slots[n->in0].value_buf);
   // residual input: the identity branch passes gy through unchanged
   if (n->in1 >= 0) {
     Slot &rs = tape->slots[n->in1];
@@ -850,31 +614,10 @@ int attention_backward(void *ctx, Tape *tape, const Node *n) {
   }
   const double fl = 10.0 * D * L->T * (double)M, by = 8.0 * M * D * e + 8.0 * L->B * H * L->T;
   const DropSpec drop = make_drop_spec(L->rec_p_attn, L->rec_seed, 1);
-  auto run = [&](int parts, hipStream_t s) {
-    return launch_attention_bwd(L->dt, qs.value, os.value, os.grad, static_cast<const float *>(n->s0), L->lengths,
-                                L->cfg.causal, drop, L->B, L->T, H, dh, nb->ptr, delta.f32(), s, parts);
-  };
-  // Worth a second stream only where dQ and dK/dV are independent kernels (the general path, whose
-  // grids leave much of the chip idle); next to the parameter-gradient stream the matrix-core kernels
-  // measured no gain from it.
-  hipStream_t s2 = L->side && attention_bwd_parts_independent(L->dt, dh) ? side_stream2() : nullptr;
-  hipError_t he;
-  if (!s2) {
-    he = timed(FL_K_ATTN_BWD, fl, by, st, [&] { return run(ATTN_BWD_ALL, st); });
-  } else {
-    // dQ and dK/dV only share their inputs (and delta): dK/dV go to the second side stream, and the
-    // layer's stream waits for them before this function returns, so no buffer outlives its readers.
-    he = timed(FL_K_ATTN_BWD, 0, 0, st, [&] { return run(ATTN_BWD_DELTA, st); });
-    hipEvent_t forked = nullptr;
-    if (he == hipSuccess && side_mark(L, &forked)) he = hipErrorUnknown;
-    if (he == hipSuccess) he = timed(FL_K_ATTN_BWD, 0.4 * fl, 0.5 * by, st, [&] { return run(ATTN_BWD_DQ, st); });
-    if (he == hipSuccess) he = hipStreamWaitEvent(s2, forked, 0);
-    if (he == hipSuccess) he = timed(FL_K_ATTN_BWD, 0.6 * fl, 0.5 * by, s2, [&] { return run(ATTN_BWD_DKV, s2); });
-    if (he == hipSuccess && !L->attn_join_event) he = hipEventCreateWithFlags(&L->attn_join_event, kEventFlags);
-    if (he == hipSuccess) he = hipEventRecord(L->attn_join_event, s2);
-    if (he == hipSuccess) he = hipStreamWaitEvent(st, L->attn_join_event, 0);
-    if (he != hipSuccess) hipStreamSynchronize(s2);  // nothing of this function may still run when its buffers go
-  }
+  hipError_t he = timed(FL_K_ATTN_BWD, fl, by, st, [&] {
+    return launch_attention_bwd(L->dt, qs.value, os.value, os.grad, static_cast<const float *>(n->s0), L->lengths, L->cfg.causal,
+                                drop, L->B, L->T, H, dh, nb->ptr, delta.f32(), st, ATTN_BWD_ALL);
+  });
   if (he != hipSuccess) {
     buf_unref(nb);
     FL_HIP(he);
@@ -924,12 +667,11 @@ int layernorm_backward(void *ctx, Tape *tape, const Node *n) {
   }
   set_grad(xs, dst, nb);
   const bool want_bias = fin && xs.colsum_param >= 0;
-  // second stage of the parameter-gradient sums: batched with the others on the parameter-gradient lane (no
-  // fork of its own: the next linear operator's fork, or the one before the last batch, covers these sums)
-  hipStream_t ps = L->side ? L->side : st;
-  side_hold(L, ws.b);
-  FL_TRY(reduce_later(L, ps, true, ws.b, parts, (size_t)3 * D, (size_t)D, want_bias ? 3 : 2, L->grads[gi], L->grads[bi],
-                      want_bias ? L->grads[xs.colsum_param] : nullptr));
+  // second stage of the parameter-gradient sums: with the weight gradients at the end of the pass
+  hold(L, ws.b);
+  FL_TRY(dw_column(L, ws.f32(), parts, 3 * D, D, true, L->grads[gi]));
+  FL_TRY(dw_column(L, ws.f32() + D, parts, 3 * D, D, true, L->grads[bi]));
+  if (want_bias) FL_TRY(dw_column(L, ws.f32() + 2 * D, parts, 3 * D, D, true, L->grads[xs.colsum_param]));
   if (want_bias) xs.colsum_done = true;
   set_grad(ys, nullptr, nullptr);
   buf_unref(ys.value_buf);
@@ -1127,7 +869,7 @@ int forward_impl(fl_layer *L, const fl_layer_params_t *params, const void *X, co
       if (h[b] < 1 || h[b] > T)
         return set_error(FL_ERR_INVALID_ARG, "lengths[%d] = %d is outside 1..T = %d", b, h[b], T);
   }
-  FL_TRY(finish_pending_join(L, st, false));
+  L->join_open = false;
   release_tape(L);
   L->B = B; L->T = T; L->M = B * T; L->stream = st; L->lengths = lengths;
   L->rec_p_attn = L->p_attn; L->rec_p_hidden = L->p_hidden; L->rec_seed = L->seed;
@@ -1171,8 +913,8 @@ int forward_static_impl(fl_layer *L, const fl_layer_params_t *params, const void
   if (B < 1 || T < 1 || B > c.max_B || T > c.max_T)
     return set_error(FL_ERR_INVALID_ARG, "B=%d T=%d outside 1..max_B=%d, 1..max_T=%d", B, T, c.max_B, c.max_T);
   if ((long)B * T > (1l << 24)) return set_error(FL_ERR_UNSUPPORTED, "B*T too large");
-  if (L->tape.recorded || L->join_pending)
-    return set_error(FL_ERR_STATE, "the handle holds a recorded forward: run its backward (and join) first");
+  if (L->tape.recorded)
+    return set_error(FL_ERR_STATE, "the handle holds a recorded forward: run its backward first");
   load_params(L, params);
   FL_TRY(check_ptrs(L->params, P_COUNT, "params"));
   const void *io[2] = {X, Y};
@@ -1265,45 +1007,26 @@ int backward_impl(fl_layer *L, const fl_layer_params_t *params, const void *dY, 
   Tape &tp = L->tape;
   tp.slots[L->slot_y].grad = const_cast<void *>(dY);
   tp.slots[L->slot_x].grad_dst = dX;
-  // the events of a fork cost the host more than tiny kernels take: small problems stay on one stream
-  L->side = g_overlap && (long)L->M * L->cfg.d_model >= (1l << 18) ? side_stream() : nullptr;
-  L->forks = 0;
-  L->tail_node = -1;
-  L->tail_split = false;
-  // (not with a deferred join: the layer's stream then goes straight on with the next layer's backward
-  // pass, and work moved onto it delays that chain -- measured +1.2 % on the 12-layer stack)
-  if (L->side && !L->defer_join)
-    for (size_t i = 0; i < tp.nodes.size(); ++i)
-      if (tp.nodes[i].backward == linear_backward) {   // first recorded = last replayed
-        L->tail_node = (int)i;
-        break;
-      }
+  dw_drop(L);
   int rc = tp.replay_reverse(L);
-  if (!rc && !L->pending_side.empty()) {  // no later operator forked: fork now
-    hipEvent_t ev;
-    hipStream_t ps;
-    rc = side_mark(L, &ev);
-    if (!rc) rc = side_begin(L, ev, &ps);
-    if (!rc) rc = run_pending_side(L, ps);
-  }
-  if (rc) {   // drop what the failed pass has collected
-    L->pending_side.clear();
-    L->reduce_jobs.clear();
-    for (Buf *&b : L->reduce_bufs) buf_unref(b);
-    L->reduce_bufs.clear();
-    L->reduce_job_main.clear();
-    L->reduce_from_main = false;
-    L->reduce_has_side = false;
-    L->tail_split = false;
-  } else {
-    rc = L->tail_split && L->side ? reduce_flush_split(L) : reduce_flush(L);
-  }
+  if (!rc) rc = dw_flush(L);
+  else dw_drop(L);
   const bool landed = rc == 0 && tp.slots[L->slot_x].grad == dX;
-  const int jrc = side_join(L, rc != 0, L->defer_join);
   release_tape(L);
   if (rc) return rc;
-  if (jrc) return jrc;
   if (!landed) return set_error(FL_ERR_STATE, "input gradient did not reach its destination");
+  L->join_open = L->defer_join;
+  return 0;
+}
+
+// Everything a backward pass enqueues is on the layer's stream: only another stream has something to wait for.
+int join_impl(fl_layer *L, hipStream_t s) {
+  if (!L->join_open) return 0;
+  L->join_open = false;
+  if (s == L->stream) return 0;
+  if (!L->join_event) FL_HIP(hipEventCreateWithFlags(&L->join_event, kEventFlags));
+  FL_HIP(hipEventRecord(L->join_event, L->stream));
+  FL_HIP(hipStreamWaitEvent(s, L->join_event, 0));
   return 0;
 }
 
@@ -1403,7 +1126,7 @@ fl_status_t fl_layer_set_deferred_join(fl_layer_t *layer, int32_t enabled) {
 fl_status_t fl_layer_join(fl_layer_t *layer, void *hip_stream) {
   FL_GUARD_BEGIN
   if (!layer) return (fl_status_t)set_error(FL_ERR_INVALID_ARG, "null argument");
-  return (fl_status_t)finish_pending_join(layer, static_cast<hipStream_t>(hip_stream), false);
+  return (fl_status_t)join_impl(layer, static_cast<hipStream_t>(hip_stream));
   FL_GUARD_END
 }
 
@@ -1460,15 +1183,10 @@ fl_status_t fl_zero_grad(fl_dtype_t dtype, int32_t n, void *const *grads, const 
 fl_status_t fl_layer_destroy(fl_layer_t *layer) {
   FL_GUARD_BEGIN
   if (!layer) return FL_OK;
-  finish_pending_join(layer, nullptr, true);
   release_tape(layer, true);  // the caller's stream may be gone by now
   if (layer->wt_fork_event) hipEventDestroy(layer->wt_fork_event);
   if (layer->wt_event) hipEventDestroy(layer->wt_event);
-  for (hipEvent_t e : layer->fork_events) hipEventDestroy(e);  // work already enqueued against them still completes
   if (layer->join_event) hipEventDestroy(layer->join_event);
-  if (layer->attn_join_event) hipEventDestroy(layer->attn_join_event);
-  if (layer->caller_read_event) hipEventDestroy(layer->caller_read_event);
-  if (layer->tail_event) hipEventDestroy(layer->tail_event);
   delete layer;
   return FL_OK;
   FL_GUARD_END

@@ -60,6 +60,22 @@ int32_t fl_test_gemm(int32_t dtype, int32_t a_kc, int32_t b_kc, const void *A, c
   return hip_status(launch_gemm(dt, a, st), "launch_gemm");
 }
 
+int32_t fl_test_dw_batch(int32_t dtype, int32_t kernel, int32_t splits, int32_t accumulate, const void *gy, const void *x,
+                         int32_t M, int32_t N, int32_t K, void *dW, void *dWt, void *db, float *partial, void *hip_stream) {
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  const int dt = dtype == FL_F32 ? DT_F32 : DT_BF16;
+  DwJob jobs[2] = {{gy, x, dW, nullptr, N, K}, {x, gy, dWt, nullptr, K, N}};
+  const ColJob col{gy, db, M, N, N, dt == DT_F32 ? 1 : 0};
+  const DwPlan plan = kernel < 0 ? dw_plan(dt, jobs, 2, M) : DwPlan{kernel, splits};
+  for (int j = 0; j < 2; ++j) jobs[j].partial = partial + (size_t)j * plan.splits * N * K;
+  int rc = hip_status(launch_dw_batch(dt, plan, jobs, 2, &col, 1, M, accumulate != 0, st), "launch_dw_batch");
+  if (rc || plan.splits == 1) return rc;
+  const size_t len = (size_t)N * K;
+  ReduceJob red[2] = {{jobs[0].partial, plan.splits, 1, len, len, {dW, nullptr, nullptr}},
+                      {jobs[1].partial, plan.splits, 1, len, len, {dWt, nullptr, nullptr}}};
+  return hip_status(launch_reduce_batch(dt, red, 2, st, accumulate != 0), "launch_reduce_batch");
+}
+
 // Times `iters` back-to-back launches of one GEMM (no epilogue) with HIP events on the stream;
 // *ms receives the mean milliseconds per launch.  Synchronises the stream.
 int32_t fl_test_gemm_time(int32_t dtype, int32_t a_kc, int32_t b_kc, const void *A, const void *B, void *C, int32_t M,

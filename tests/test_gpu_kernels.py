@@ -126,6 +126,32 @@ def test_gemm_bf16_pipelined_variants(variant, mode, shape):
         b.lib().fl_test_gemm_force_variant(-1)
 
 
+@pytest.mark.parametrize("dtype,kernel,splits", [("bf16", k, s) for k in (-1, 0, 1, 2, 3, 4) for s in (1, 3) if k >= 0 or s == 1] +
+                         [("f32", k, s) for k in (-1, 3, 4) for s in (1, 3) if k >= 0 or s == 1])
+@pytest.mark.parametrize("shape", [(1, 8, 8), (63, 72, 40), (257, 264, 136), (200, 520, 8), (641, 256, 384)])
+def test_weight_gradient_batch(dtype, kernel, splits, shape):
+    """The launch behind a backward pass's parameter gradients on each of its kernels: token counts below, at and past
+    whole k-tiles, ragged tiles, token ranges with partial sums, added to what the buffers hold or not."""
+    b = _lib()
+    M, N, K = shape
+    kt = 64 if dtype == "bf16" else 32
+    if splits > 1 and (splits - 1) * (-(-(-(-M // splits)) // kt) * kt) >= M:
+        pytest.skip("a token range would be empty")
+    rng = np.random.default_rng(M + N)
+    gy, x = quantise(rng.standard_normal((M, N)), dtype), quantise(rng.standard_normal((M, K)), dtype)
+    ref = gy.astype(np.float64).T @ x.astype(np.float64)
+    tgy, tx = to_dev(gy, dtype), to_dev(x, dtype)
+    part = empty_dev((2 * max(splits, 16) * N * K,), "f32")
+    for accumulate in (0, 1):
+        was = [quantise(rng.standard_normal(s), dtype) if accumulate else None for s in ((N, K), (K, N), (N,))]
+        out = [to_dev(w, dtype) if accumulate else empty_dev(s, dtype) for w, s in zip(was, ((N, K), (K, N), (N,)))]
+        b.check(b.lib().fl_test_dw_batch(dt_code(dtype), kernel, splits, accumulate, tgy.data_ptr(), tx.data_ptr(), M, N, K,
+                                         *[o.data_ptr() for o in out], part.data_ptr(), stream_ptr()))
+        torch_mod().cuda.synchronize()
+        for o, w, r in zip(out, was, (ref, ref.T, gy.astype(np.float64).sum(0))):
+            assert rel_err(to_np(o), r + (w if accumulate else 0.0)) <= _tol(dtype), accumulate
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("act", [0, 1, 2])
 def test_gemm_forward_epilogue(dtype, act):
