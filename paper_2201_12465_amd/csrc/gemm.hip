@@ -240,8 +240,7 @@ int gemm_pick_splits(int dt, int M, int N, int K) {
     want = (int)((432 + tiles / 2) / tiles);
     if (want > 6) want = 6;
   } else if (gemm_f32_small_applies(M, N)) {
-    // 32 x 32 tiles with k split inside the workgroup: a wavefront's chain is K/8 MFMAs of 64 clocks
-    // (3.4 us at K = 1024), less than a second-stage launch costs, until K gets long
+    // too few tiles to fill the chip either way: a split pays for its second stage only where K is long
     want = (K + 4095) / 4096;
   } else {
     want = (int)((512 + tiles - 1) / tiles);
@@ -285,14 +284,17 @@ hipError_t launch_gemm(int dt, const GemmArgs &a, hipStream_t stream) {
   d.tiles_n = (a.N + BN - 1) / BN;
   // every k-range must be non-empty, or its partial slab would stay unwritten
   if ((long)(splits - 1) * kps >= a.K) return hipErrorInvalidValue;
-  if (dt == DT_BF16 && gemm_pipe_eligible(a, kps)) {
+  const int force_tmw = forced_gemm_tile_height(), forced = forced_gemm_pipe_variant();
+  const bool pipe = dt == DT_BF16 && gemm_pipe_eligible(a, kps);
+  const int small = forced >= 20 ? forced - 20 : forced == -1 && !force_tmw ? gemm_small_pick(dt, a.a_kc, a.M, a.N, a.K, pipe) : -1;
+  if (small >= 0 && (long)a.M * a.lda < (1l << 31) && (long)(a.b_kc ? a.N : a.K) * a.ldb < (1l << 31))
+    return launch_gemm_small(dt, a, &d, splits, small, stream);
+  if (pipe) {
     int variant = gemm_pipe_pick_variant(a.a_kc, a.b_kc, a.M, a.N, a.K, a.alone);
     if (variant > 0 && d.drop_where) variant = 0;  // the dropout steps exist in the 128x128 / 2-stage instance only,
     if (d.drop_where && !(a.a_kc && a.b_kc)) variant = -2;  // and there for k-contiguous operands only
     if (variant >= 0) return launch_gemm_bf16_pipe(a, &d, splits, variant, stream);
   }
-  const int force_tmw = forced_gemm_tile_height();
-  if (dt == DT_F32 && !force_tmw && gemm_f32_small_applies(a.M, a.N)) return launch_gemm_f32_small(a, &d, splits, stream);
   // fewer than 1.5 full tiles per CU: halve the tile height so that twice as many workgroups run
   int tmw = (long)d.tiles_m * d.tiles_n * splits < 384 && a.M > 64 ? 1 : 2;
   if (force_tmw) tmw = force_tmw;

@@ -48,7 +48,7 @@ hipError_t launch_gemm(int dt, const GemmArgs &a, hipStream_t stream);
 int gemm_pick_splits(int dt, int M, int N, int K);
 // Kernel-selection overrides (select.cpp).  The getters are constants in the library that ships; the
 // setters exist only in the test build (FL_TEST_EXPORTS).
-int forced_gemm_pipe_variant();   // -1 = automatic; >= 0 forces a tile/stage variant; -2 = never use the pipelined kernel
+int forced_gemm_pipe_variant();   // -1 = automatic; >= 0 forces a tile/stage variant; -2 = only gemm.hip; 20.. = gemm_small.hip's variants
 int forced_gemm_tile_height();    // gemm.hip kernel: 0 automatic, 1 = 64x128 tiles, 2 = 128x128 tiles
 bool forced_general_attention();  // general (vector-ALU) attention kernels for every head size
 bool forced_unfused_attention_bwd();  // never the one-kernel attention backward
@@ -60,11 +60,10 @@ void attention_force_unfused_bwd(bool on);
 void dw_force_kernel(int k);
 #endif
 
-// fp32 outputs with few tiles (gemm_f32_small.hip): 32 x 32 tiles, the four wavefronts of a workgroup
-// split k.  launch_gemm uses it when gemm_f32_small_applies and no tile height is forced.
+// Outputs with few tiles, A k-contiguous (gemm_small.hip): launch_gemm uses it where gemm_small_pick returns a variant
+// (pipe_eligible: what gemm_pipe_eligible says about the problem).
+int gemm_small_pick(int dt, bool a_kc, int M, int N, int K, bool pipe_eligible);
 bool gemm_f32_small_applies(int M, int N);
-hipError_t launch_gemm_f32_small(const GemmArgs &a, const void *gemm_dev, int splits, hipStream_t s);
-
 hipError_t launch_gemm_small(int dt, const GemmArgs &a, const void *gemm_dev, int splits, int variant, hipStream_t s);
 
 // The pipelined bf16 kernel (gemm_pipe.hip); launch_gemm uses it whenever the problem is eligible.

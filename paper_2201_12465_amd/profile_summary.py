@@ -45,6 +45,11 @@ def classify(name: str) -> str:
             a, bb = (x in ("true", "1") for x in m.groups())
             return {(True, True): "gemm_nt", (True, False): "gemm_nn", (False, False): "gemm_tn"}.get((a, bb), "gemm")
         return "gemm_nt"
+    if "gemm_dw" in n:   # every weight gradient of a backward pass
+        return "gemm_tn"
+    if "gemm_small" in n:   # A is always k-contiguous; the layout flag of B is the last one in front of the tile counts
+        m = re.search(r"gemm_small<.*?(true|false), \d", n) or re.search(r"gemm_smallI\w+?Lb1ELb([01])E", n)
+        return {"true": "gemm_nt", "1": "gemm_nt"}.get(m.group(1), "gemm_nn") if m else "gemm"
     if "gemm_f32_small" in n:
         m = re.search(r"gemm_f32_small(?:<|ILb)(true|false|1|0)(?:, |ELb)(true|false|1|0)", n)
         if m:

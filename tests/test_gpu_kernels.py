@@ -126,6 +126,37 @@ def test_gemm_bf16_pipelined_variants(variant, mode, shape):
         b.lib().fl_test_gemm_force_variant(-1)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("mode", ["nt", "nn"])
+@pytest.mark.parametrize("variant", [20, 21, 22])
+@pytest.mark.parametrize("shape", [(1, 8, 8), (24, 72, 200), (65, 136, 64), (97, 200, 776), (33, 64, 1032)])
+def test_gemm_few_tiles(dtype, mode, variant, shape):
+    """The kernel for few output tiles on each of its tile shapes: fewer k-tiles than wavefronts, a ragged last k-tile,
+    rows and columns at and past a tile's edge; plain, and with every step of the forward epilogue."""
+    b = _lib()
+    M, N, K = shape
+    rng = np.random.default_rng(hash((mode, shape)) % 2**32)
+    A = quantise(rng.standard_normal((M, K)), dtype)
+    W = quantise(rng.standard_normal((N, K)) * 0.2, dtype)
+    bias, res = quantise(rng.standard_normal(N), dtype), quantise(rng.standard_normal((M, N)), dtype)
+    u = A.astype(np.float64) @ W.astype(np.float64).T
+    tA, tW, tb, tr = to_dev(A, dtype), to_dev(W if mode == "nt" else W.T.copy(), dtype), to_dev(bias, dtype), to_dev(res, dtype)
+    b.lib().fl_test_gemm_force_variant(variant)
+    try:
+        dC, dU = empty_dev((M, N), dtype), empty_dev((M, N), dtype)
+        b.check(b.lib().fl_test_gemm(dt_code(dtype), 1, mode == "nt", tA.data_ptr(), tW.data_ptr(), dC.data_ptr(), M, N, K, None,
+                                     None, 0, None, 0, None, 1, None, stream_ptr()))
+        torch_mod().cuda.synchronize()
+        assert rel_err(to_np(dC), u) <= _tol(dtype)
+        b.check(b.lib().fl_test_gemm(dt_code(dtype), 1, mode == "nt", tA.data_ptr(), tW.data_ptr(), dC.data_ptr(), M, N, K,
+                                     tb.data_ptr(), tr.data_ptr(), 2, dU.data_ptr(), 0, None, 1, None, stream_ptr()))
+        torch_mod().cuda.synchronize()
+        assert rel_err(to_np(dU), u + bias) <= _tol(dtype)
+        assert rel_err(to_np(dC), orc.act_fwd(u + bias, "gelu") + res) <= _tol(dtype)
+    finally:
+        b.lib().fl_test_gemm_force_variant(-1)
+
+
 @pytest.mark.parametrize("dtype,kernel,splits", [("bf16", k, s) for k in (-1, 0, 1, 2, 3, 4) for s in (1, 3) if k >= 0 or s == 1] +
                          [("f32", k, s) for k in (-1, 3, 4) for s in (1, 3) if k >= 0 or s == 1])
 @pytest.mark.parametrize("shape", [(1, 8, 8), (63, 72, 40), (257, 264, 136), (200, 520, 8), (641, 256, 384)])
