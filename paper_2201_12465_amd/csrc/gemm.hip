@@ -286,7 +286,7 @@ hipError_t launch_gemm(int dt, const GemmArgs &a, hipStream_t stream) {
   if ((long)(splits - 1) * kps >= a.K) return hipErrorInvalidValue;
   const int force_tmw = forced_gemm_tile_height(), forced = forced_gemm_pipe_variant();
   const bool pipe = dt == DT_BF16 && gemm_pipe_eligible(a, kps);
-  const int small = forced >= 20 ? forced - 20 : forced == -1 && !force_tmw ? gemm_small_pick(dt, a.a_kc, a.M, a.N, a.K, pipe) : -1;
+  const int small = forced >= 20 ? forced - 20 : forced == -1 && !force_tmw ? gemm_small_pick(dt, a.a_kc, a.M, a.N, a.K, pipe, a.act == 2 || a.dact == 2) : -1;
   if (small >= 0 && (long)a.M * a.lda < (1l << 31) && (long)(a.b_kc ? a.N : a.K) * a.ldb < (1l << 31))
     return launch_gemm_small(dt, a, &d, splits, small, stream);
   if (pipe) {

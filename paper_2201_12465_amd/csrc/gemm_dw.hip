@@ -173,12 +173,17 @@ long tiles_of(const DwJob *jobs, int n, int bm, int bn) {
   return t;
 }
 
-// kernel of a plan: its tile, how many of its workgroups a CU holds, and microseconds per k-tile when the CU is full
-struct DwKernel { int bm, bn, per_cu; double us_per_ktile; };
-const DwKernel kBf16[5] = {{256, 256, 1, 1.41}, {256, 128, 1, 0.94}, {128, 128, 2, 1.12}, {64, 64, 2, 0.40}, {32, 32, 2, 0.20}};
+// kernel of a plan: its tile, the part of a launch that does not depend on the tokens, and microseconds per k-tile (64
+// tokens; fp32: 32) of a CU that works on one tile, and per tile when it works on several
+struct DwKernel { int bm, bn; double fix, one, more; };
+const DwKernel kBf16[5] = {{256, 256, 8.0, 1.60, 1.60}, {256, 128, 7.0, 1.05, 1.05}, {128, 128, 6.0, 0.56, 0.56}, {64, 64, 4.5, 0.20, 0.20}, {32, 32, 3.5, 0.10, 0.16}};
+const DwKernel kF32[2] = {{64, 64, 5.0, 0.53, 0.72}, {32, 32, 3.5, 0.18, 0.24}};
 
 }  // namespace
 
+// The kernel and token split with the least time by that table, splits paying for their partial sums (written and read
+// at 5 TB/s) and a second launch.  BERT-base shape (4096 tokens): 256 x 128 unsplit, 76 us where the four launches and
+// their second stages took 124; 12608 tokens: 256 x 256 in two ranges, 190 us against 250.
 DwPlan dw_plan(int dt, const DwJob *jobs, int njobs, int M) {
   DwPlan best{dt == DT_F32 ? DW_SMALL32 : DW_128, 1};
   const int forced = forced_dw_kernel();
@@ -187,17 +192,15 @@ DwPlan dw_plan(int dt, const DwJob *jobs, int njobs, int M) {
   for (int j = 0; j < njobs; ++j) elems += (long)jobs[j].N * jobs[j].K;
   for (int k = 0; k < 5; ++k) {
     if (forced >= 0 ? k != forced : dt == DT_F32 && k < DW_SMALL64) continue;
-    const DwKernel &K = kBf16[k];
+    const DwKernel &K = dt == DT_F32 ? kF32[k - DW_SMALL64] : kBf16[k];
     const int kt = dt == DT_F32 ? 32 : KT, nk = (M + kt - 1) / kt;
-    const long tiles = tiles_of(jobs, njobs, K.bm, K.bn), slots = 256l * K.per_cu;
-    // fp32: the matrix cores take 64 clocks for two k of a 32 x 32 tile
-    const double per = dt == DT_F32 ? (k == DW_SMALL32 ? 0.30 : 1.05) : K.us_per_ktile;
+    const long tiles = tiles_of(jobs, njobs, K.bm, K.bn);
     for (int s = 1; s <= 16 && s <= nk; ++s) {
       const int per_split = (nk + s - 1) / s;
       if ((long)(s - 1) * per_split >= nk) continue;   // an empty range
-      const long rounds = (tiles * s + slots - 1) / slots;
-      double us = rounds * (4.0 + per_split * per);
-      if (s > 1) us += 5.0 + (double)elems * s * 8 / 5.0e6;   // partial sums written and read at 5 TB/s, and a launch
+      const long n = (tiles * s + 255) / 256;          // tiles of the fullest CU
+      double us = K.fix + n * per_split * (n > 1 ? K.more : K.one) + (n - 1) * (k <= DW_256x128 ? K.fix : 1.0);
+      if (s > 1) us += 5.0 + (double)elems * s * 8 / 5.0e6;
       if (us < best_us) best_us = us, best = {k, s};
     }
   }

@@ -73,7 +73,7 @@ hipError_t launch_v(const GemmArgs &a, const GemmDev &d, int splits, int v, hipS
 //   3072: 28.3 -> 13.0; 1001 x 2048 x 512: 8.9 -> 7.2.
 //   fp32: a fixed part plus the matrix cores' time for the fullest CU's tiles, 5-7.5 ns per k and 32x32 block (the
 //   64 x 64 tiles reuse fragments: 4.1).  1024 x 256 x 1024: 12.4 -> 8.9; 2048 x 512 x 2048: 51 -> 39.
-int gemm_small_pick(int dt, bool a_kc, int M, int N, int K, bool pipe_eligible) {
+int gemm_small_pick(int dt, bool a_kc, int M, int N, int K, bool pipe_eligible, bool gelu) {
   if (!a_kc) return -1;
   const int rows[3] = {64, 96, 128};
   const long tm32 = (M + 31) / 32, tn32 = (N + 31) / 32, tn64 = (N + 63) / 64, tm64 = (M + 63) / 64;
@@ -95,7 +95,8 @@ int gemm_small_pick(int dt, bool a_kc, int M, int N, int K, bool pipe_eligible) 
   if (dt == DT_F32) return gemm_f32_small_applies(M, N) ? best : -1;
   if (!pipe_eligible) return tiles[2] <= 2048 ? best : -1;   // a ragged k: the alternative is the register-staged kernel
   const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-  const double pipe_us = 4.6 + (double)((t128 + 255) / 256) * 256 * K * 2 / 69e3;
+  // (GELU and its derivative: every thread of a workgroup walks the epilogue here, half of them there)
+  const double pipe_us = 4.6 + (gelu ? 3.0 : 0.0) + (double)((t128 + 255) / 256) * 256 * K * 2 / 69e3;
   return tiles[2] <= 1024 && best_us < pipe_us ? best : -1;
 }
 

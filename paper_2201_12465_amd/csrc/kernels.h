@@ -51,6 +51,7 @@ int gemm_pick_splits(int dt, int M, int N, int K);
 int forced_gemm_pipe_variant();   // -1 = automatic; >= 0 forces a tile/stage variant; -2 = only gemm.hip; 20.. = gemm_small.hip's variants
 int forced_gemm_tile_height();    // gemm.hip kernel: 0 automatic, 1 = 64x128 tiles, 2 = 128x128 tiles
 bool forced_general_attention();  // general (vector-ALU) attention kernels for every head size
+int forced_f32_key_groups();      // fp32 attention: wavefronts on the same rows, 1 / 2 / 4; 0 = automatic
 bool forced_unfused_attention_bwd();  // never the one-kernel attention backward
 #ifdef FL_TEST_EXPORTS
 void gemm_pipe_force_variant(int v);
@@ -58,11 +59,12 @@ void gemm_force_tile_height(int tmw);
 void attention_force_general(bool on);
 void attention_force_unfused_bwd(bool on);
 void dw_force_kernel(int k);
+void attention_force_f32_key_groups(int kg);
 #endif
 
 // Outputs with few tiles, A k-contiguous (gemm_small.hip): launch_gemm uses it where gemm_small_pick returns a variant
-// (pipe_eligible: what gemm_pipe_eligible says about the problem).
-int gemm_small_pick(int dt, bool a_kc, int M, int N, int K, bool pipe_eligible);
+// (pipe_eligible: what gemm_pipe_eligible says about the problem; gelu: GELU or its derivative in the epilogue).
+int gemm_small_pick(int dt, bool a_kc, int M, int N, int K, bool pipe_eligible, bool gelu);
 bool gemm_f32_small_applies(int M, int N);
 hipError_t launch_gemm_small(int dt, const GemmArgs &a, const void *gemm_dev, int splits, int variant, hipStream_t s);
 

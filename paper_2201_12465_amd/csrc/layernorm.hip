@@ -424,11 +424,8 @@ hipError_t ln_bwd_t(const void *dy, const void *x, const float *mean, const floa
 int ln_bwd_parts(int M, int D) {
   const int nw = ln_waves(D);
   int parts = (M + 2 * nw - 1) / (2 * nw);  // at least two rows per wave
-  // At most 160 workgroups, not one per CU: alone the kernel is 3 % slower with them (11.9 against 11.5 us on
-  // 4096 x 768), but inside the backward pass it runs beside a weight-gradient GEMM of the other stream, and
-  // leaving that kernel 96 CUs to itself is worth more (BERT-base step 0.381 -> 0.375 ms with 128-160, speech
-  // and ViT shapes -0.7 % and -0.9 % with 144-192; 512 workgroups: +0.8 % on those two).
-  if (parts > 160) parts = 160;
+  // at most one workgroup per CU (4096 x 768: 11.5 us against 11.9 with 160)
+  if (parts > 256) parts = 256;
   const int rows = (M + parts - 1) / parts;
   return (M + rows - 1) / rows;  // no empty workgroup
 }
