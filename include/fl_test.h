@@ -97,6 +97,8 @@ int32_t fl_test_dropout_mul(int32_t dtype, const void *in, void *out, int32_t M,
 
 /* on != 0: bf16 attention uses the general (vector-ALU) kernels instead of the MFMA ones. */
 void fl_test_attention_force_general(int32_t on);
+/* fp32 attention on the matrix cores: wavefronts that share a group of rows, 1, 2 or 4; 0 = automatic. */
+void fl_test_attention_force_f32_key_groups(int32_t kg);
 /* on != 0: bf16 attention backward always runs as the dQ kernel followed by the dK/dV kernel(s), also where
  * the one-kernel backward (head size 64, T <= 224) would apply. */
 void fl_test_attention_force_unfused_bwd(int32_t on);

@@ -464,6 +464,21 @@ def test_attention_forward_backward(dtype, case, causal, p_drop):
         b.lib().fl_test_attention_force_general(0)
 
 
+@pytest.mark.parametrize("causal,p_drop", [(False, 0.0), (True, 0.3)])
+@pytest.mark.parametrize("kg", [1, 2, 4])
+@pytest.mark.parametrize("case", [(2, 31, 2, 32, [31, 2]), (1, 97, 1, 64, [65]), (2, 130, 2, 48, [130, 33]), (1, 257, 1, 96, None),
+                                  (1, 129, 1, 128, [128])])
+def test_attention_f32_wavefronts_on_the_same_rows(case, kg, causal, p_drop):
+    """fp32 attention with 1, 2 and 4 wavefronts sharing 32 rows: fewer blocks than wavefronts, lengths that leave some of
+    them without a key, rows past the end, padded head sizes."""
+    b = _lib()
+    b.lib().fl_test_attention_force_f32_key_groups(kg)
+    try:
+        _attention_case(b, "f32", case, causal, p_drop)
+    finally:
+        b.lib().fl_test_attention_force_f32_key_groups(0)
+
+
 @pytest.mark.parametrize("causal,p_drop", [(False, 0.0), (True, 0.0), (False, 0.2), (True, 0.35)])
 def test_attention_forward_large_head_with_a_sequence_of_one_key(causal, p_drop):
     """Forward only (output and log-sum-exp against the oracle): with one key and dropout the reference gradient
