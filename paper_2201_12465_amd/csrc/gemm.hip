@@ -290,9 +290,8 @@ hipError_t launch_gemm(int dt, const GemmArgs &a, hipStream_t stream) {
   if (small >= 0 && (long)a.M * a.lda < (1l << 31) && (long)(a.b_kc ? a.N : a.K) * a.ldb < (1l << 31))
     return launch_gemm_small(dt, a, &d, splits, small, stream);
   if (pipe) {
-    int variant = gemm_pipe_pick_variant(a.a_kc, a.b_kc, a.M, a.N, a.K, a.alone);
-    if (variant > 0 && d.drop_where) variant = 0;  // the dropout steps exist in the 128x128 / 2-stage instance only,
-    if (d.drop_where && !(a.a_kc && a.b_kc)) variant = -2;  // and there for k-contiguous operands only
+    int variant = gemm_pipe_pick_variant(a.a_kc, a.b_kc, a.M, a.N, a.K, a.alone, d.drop_where != 0);
+    if (d.drop_where && (!a.a_kc || !gemm_pipe_takes_dropout(variant))) variant = a.a_kc && variant >= 0 ? 0 : -2;
     if (variant >= 0) return launch_gemm_bf16_pipe(a, &d, splits, variant, stream);
   }
   // fewer than 1.5 full tiles per CU: halve the tile height so that twice as many workgroups run

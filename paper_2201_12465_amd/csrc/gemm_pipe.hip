@@ -9,7 +9,7 @@
 //   A wave-level load writes 64 consecutive 16-byte chunks of LDS; WHICH global chunk a
 //   lane fetches is free, and that is where the bank-conflict swizzle is applied:
 //     k-contiguous tile  [rows][64 k]   : chunk c of row r sits at position c ^ ((r>>1)&7)
-//     k-major tile       [64 k][rows]   : chunk c of k-row k sits at position c ^ ((k&3)<<2)
+//     k-major tile       [64 k][rows]   : chunk c of k-row k sits at position c ^ km_swizzle(k)
 //   Both make the MFMA fragment reads (16-byte row reads, and the transposing
 //   ds_read_b64_tr_b16 for k-major tiles) touch every bank once per 32 lanes.
 // * Rows past the end of an operand are clamped to the last valid row (their products land in
@@ -34,6 +34,13 @@ typedef __attribute__((address_space(3))) s16x4_t *lds_s16x4_ptr;
 
 template <int N> __device__ __forceinline__ void wait_vmcnt_le() { FL_WAIT_VMCNT(N); }
 
+// Chunk swizzle of a k-major tile of R rows.  A transposing read touches 64 bytes of each of four consecutive k-rows,
+// which must fall into different quarters of the 256 bytes of banks: rows of a multiple of 256 bytes (R = 128, 256) need
+// all four shifted apart, rows of an odd multiple of 128 (R = 192) the two pairs, odd multiples of 64 none.
+template <int R> __device__ __forceinline__ int km_swizzle(int k) {
+  return R % 128 == 0 ? (k & 3) << 2 : R % 64 == 0 ? ((k >> 1) & 1) << 2 : 0;
+}
+
 // One operand's staging plan for this wave: element offsets (from the operand base) of the chunks
 // its lanes fetch, for each of its NOPS wave-level loads per k-tile.
 template <bool KC, int R, int NW> struct Stager {
@@ -49,7 +56,7 @@ template <bool KC, int R, int NW> struct Stager {
         off[j] = min(row0 + r, nrows - 1) * ld + kbeg + c * 8;
       } else {
         constexpr int CPR = R / 8;
-        const int k = P / CPR, c = (P % CPR) ^ ((k & 3) << 2);
+        const int k = P / CPR, c = (P % CPR) ^ km_swizzle<R>(k);
         off[j] = (kbeg + k) * ld + min(row0 + c * 8, nrows - 8);
       }
     }
@@ -76,7 +83,7 @@ __device__ __forceinline__ bf16x8_t frag(const unsigned char *stage, int r0, int
     const int g = lane >> 4, s = lane & 15;
     const int kb = kk * 16 + (g >> 1) * 8 + (s >> 2);
     const int rowpos = r0 + (g & 1) * 16 + 4 * (s & 3);
-    const int c = (rowpos >> 3) ^ ((kb & 3) << 2);
+    const int c = (rowpos >> 3) ^ km_swizzle<R>(kb);
     const unsigned char *a = stage + kb * (R * 2) + c * 16 + (rowpos & 7) * 2;
     s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)a);
     s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(a + 4 * R * 2));
@@ -246,27 +253,27 @@ hipError_t launch_cfg_d(GemmDev d, int splits, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Dropout in the epilogue exists for the 128x128 / 2-stage variant (the forward GEMMs in training mode).
+// the epilogue kinds of the instances the layer runs on (see gemm_epi_kind), with or without the dropout steps
+template <bool AKC, bool BKC, int BM, int BN, int NS, int WM, int WN, int KG, bool DROP>
+hipError_t launch_kind(const GemmDev &d, int splits, hipStream_t s) {
+  const int kind = gemm_epi_kind(d.partial != nullptr, d.act, d.dact, d.preact != nullptr);
+  if (kind == EPI_PLAIN) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, DROP, KG, EPI_PLAIN>(d, splits, s);
+  if (!DROP && kind == EPI_PARTIAL) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, false, KG, EPI_PARTIAL>(d, splits, s);
+  if (kind == EPI_LIGHT) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, DROP, KG, EPI_LIGHT>(d, splits, s);
+  if (kind == EPI_GELU_FWD) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, DROP, KG, EPI_GELU_FWD>(d, splits, s);
+  if (kind == EPI_GELU_BWD) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, DROP, KG, EPI_GELU_BWD>(d, splits, s);
+  return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, DROP, KG>(d, splits, s);
+}
 template <bool AKC, bool BKC, int BM, int BN, int NS, int WM = 2, int WN = 2, int KG = 1>
 hipError_t launch_cfg(const GemmDev &d, int splits, hipStream_t s) {
-  if (d.drop_where) {
-    if constexpr (AKC && BKC && NS == 2 && BM == 128 && BN == 128)
-      return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, true, KG>(d, splits, s);
-    else
-      return hipErrorInvalidValue;
-  }
-  // the instances the layer runs on carry only the epilogue steps of their launch (see gemm_epi_kind)
   constexpr bool specialised = (BM == 128 && BN == 128 && WM == 2 && WN == 2 && ((NS == 2 && KG == 1) || (NS == 3 && KG == 2))) ||
-                               (BM == 256 && BN == 192) || (BN == 128 && (BM == 160 || BM == 96));
-  if constexpr (specialised) {
-    const int kind = gemm_epi_kind(d.partial != nullptr, d.act, d.dact, d.preact != nullptr);
-    if (kind == EPI_PLAIN) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, false, KG, EPI_PLAIN>(d, splits, s);
-    if (kind == EPI_PARTIAL) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, false, KG, EPI_PARTIAL>(d, splits, s);
-    if (kind == EPI_LIGHT) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, false, KG, EPI_LIGHT>(d, splits, s);
-    if (kind == EPI_GELU_FWD) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, false, KG, EPI_GELU_FWD>(d, splits, s);
-    if (kind == EPI_GELU_BWD) return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, false, KG, EPI_GELU_BWD>(d, splits, s);
+                               (BM == 256 && BN == 192) || (BN == 128 && (BM == 160 || BM == 96)) || (BM == 256 && BN == 256 && WN == 4);
+  if (d.drop_where) {   // (see gemm_pipe_takes_dropout)
+    if constexpr (AKC && specialised && BM <= 160) return launch_kind<AKC, BKC, BM, BN, NS, WM, WN, KG, true>(d, splits, s);
+    else return hipErrorInvalidValue;
   }
-  return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, false, KG>(d, splits, s);
+  if constexpr (specialised) return launch_kind<AKC, BKC, BM, BN, NS, WM, WN, KG, false>(d, splits, s);
+  else return launch_cfg_d<AKC, BKC, BM, BN, NS, WM, WN, false, KG>(d, splits, s);
 }
 
 template <bool AKC, bool BKC>
@@ -281,14 +288,14 @@ hipError_t launch_layout(const GemmDev &d, int splits, int variant, hipStream_t 
     case 6: return launch_cfg<AKC, BKC, 256, 128, 3, 4, 2>(d, splits, s);
     case 8: return launch_cfg<AKC, BKC, 128, 128, 2, 2, 2, 2>(d, splits, s);
     case 9: return launch_cfg<AKC, BKC, 128, 128, 3, 2, 2, 2>(d, splits, s);
-    case 10:  // 160 rows: the same restriction for a k-major A operand
+    case 10:
       if constexpr (AKC) return launch_cfg<AKC, BKC, 160, 128, 2, 1, 4>(d, splits, s);
       else return hipErrorInvalidValue;
-    case 11:  // 96 rows: likewise
+    case 11:
       if constexpr (AKC) return launch_cfg<AKC, BKC, 96, 128, 2, 1, 4>(d, splits, s);
       else return hipErrorInvalidValue;
-    case 7:  // 192 columns: the k-major swizzle needs a power-of-two row length, so k-contiguous operands only
-      if constexpr (AKC && BKC) return launch_cfg<AKC, BKC, 256, 192, 2, 4, 2>(d, splits, s);
+    case 7:  // used for y = x W^T and dx = dy W only
+      if constexpr (AKC) return launch_cfg<AKC, BKC, 256, 192, 2, 4, 2>(d, splits, s);
       else return hipErrorInvalidValue;
   }
   return hipErrorInvalidValue;
@@ -309,18 +316,29 @@ void gemm_pipe_tile(int variant, int *bm, int *bn) {
   *bn = t[variant][1];
 }
 
-int gemm_pipe_pick_variant(bool a_kc, bool b_kc, int M, int N, int K, bool alone) {
-  const int forced = forced_gemm_pipe_variant();
-  if (forced != -1) return (forced == 7 && !(a_kc && b_kc)) || ((forced == 10 || forced == 11) && !a_kc) ? -2 : forced;
-  (void)K;
-  // Measured inside the layer (whole training steps, same box, libraries alternating), since a loop over one
-  // launch flatters whatever profits most from warm caches.
-  // dy^T x (both operands k-major, split over the tokens) and dy W (one k-major operand, used where forward
-  // left no transposed weights behind): 128x128 tiles, 2 stages, two workgroups per CU.  2-3 % of a step
-  // against the register-staged kernel in gemm.hip on the BERT-base, speech and ViT shapes (0.404 -> 0.394,
-  // 0.799 -> 0.779, 12.03 -> 11.68 ms for dy^T x; 12.07 -> 11.75 ms for dy W); the variants with three
-  // stages or two wavefront groups per tile hold more LDS and slow the kernels they run beside.
-  if (!a_kc && !b_kc) return 0;
+// dropout steps in the epilogue: not with the large wavefront tiles, which have no registers for the generator
+bool gemm_pipe_takes_dropout(int variant) { return variant == 0 || variant == 9 || variant == 10 || variant == 11; }
+
+namespace {
+// Time of a launch that has the chip to itself, in us: tiles per CU (of the fullest) x k-tiles x what a CU takes for one
+// k-tile of one tile, plus a fixed part (per tile, where a CU holds one workgroup).  Fitted to launches of 4096-16384
+// rows, N, K = 768..4096, k-contiguous and k-major B alike (they do not differ); within 6 % of all of them.
+double pipe_time(int variant, int M, int N, int K) {
+  int bm, bn;
+  gemm_pipe_tile(variant, &bm, &bn);
+  const double n = (double)(((long)((M + bm - 1) / bm) * ((N + bn - 1) / bn) + 255) / 256), nk = K / (double)KT;
+  switch (variant) {
+    case 0: return 4.0 + n * nk * 0.617;
+    case 5: return n * (8.2 + nk * 1.65);
+    case 7: return n * (8.5 + nk * 1.06);
+    case 9: return n * (5.2 + nk * 0.54);
+    case 10: return 5.5 + n * nk * (n > 2 ? 0.70 : 0.59);
+    case 11: return 5.5 + n * nk * (n > 2 ? 0.515 : 0.42);
+  }
+  return 1e30;
+}
+// What was found by hand inside whole training steps.
+int pipe_base_variant(bool b_kc, int M, int N, bool alone) {
   // More 128x128 tiles than the chip holds at two workgroups per CU, but not with 160x128 tiles: one round
   // instead of one and a bit (12608 x 768 outputs: 594 tiles against 474; dy W at k = 3072 / 2304 / 768 alone:
   // 83 -> 66, 64 -> 51, 28 -> 22 us).
@@ -328,34 +346,39 @@ int gemm_pipe_pick_variant(bool a_kc, bool b_kc, int M, int N, int K, bool alone
   const bool one_round_160 = tiles128 > slots && (long)((M + 159) / 160) * ((N + 127) / 128) <= slots;
   // One round of 128x128 tiles that leaves a quarter of the places empty, where 96x128 tiles fill them (8000 x 768
   // outputs: 378 tiles against 504; on their own 57 -> 48, 42 -> 38, 20 -> 17.5 us at k = 3072 / 2304 / 768).  Only with
-  // more tiles than CUs (below that the two-k-group variant is ahead), and only for a launch that has the chip to
-  // itself: in the backward pass the places that 128x128 tiles leave empty take the weight-gradient workgroups of
-  // the other lane, and whole steps of the speech shape are slower with the rule there (0.725 -> 0.738 ms).
+  // more tiles than CUs (below that the two-k-group variant is ahead), and only for a launch that has the chip to itself.
   const bool one_round_96 = alone && tiles128 > 256 && 5 * tiles128 <= 4 * slots && (long)((M + 95) / 96) * ((N + 127) / 128) <= slots;
-  if (a_kc && !b_kc) return one_round_160 ? 10 : one_round_96 ? 11 : 0;
-  if (!(a_kc && b_kc)) return -2;
-  // the same for k-contiguous operands, ahead of one 75-78 %-full round of 256x192 tiles (ViT stack, libraries
-  // alternating: 10.64 ms per step -> 10.58 with the rule for dy W alone -> 10.46 with both; BERT-base shape,
-  // where it takes the fused projection: 0.3703 -> 0.3682 ms)
   if (one_round_160) return 10;
-  // Both operands k-contiguous:
-  // 256x192 tiles on 8 wavefronts halve the L1 and LDS traffic per flop and win when they fill the
-  // chip in whole rounds (one workgroup per CU); otherwise 128x128 / 2 stages, two workgroups per CU.
-  if (N % 192 == 0) {
-    const long tiles = (long)((M + 255) / 256) * (N / 192);
-    const long rounds = (tiles + 255) / 256;
-    // one round of tiles: worth it from 160 tiles up; several rounds: only if the last one is nearly full
-    // (12608 x 3072, 800 tiles = 3.1 rounds: 88 us against 81 with 128x128 tiles; 8000 x 3072, 512 tiles: 47.5
-    // against 51)
+  if (b_kc && N % 192 == 0) {
+    // 256x192 tiles on 8 wavefronts halve the L1 and LDS traffic per flop and win when they fill the
+    // chip in whole rounds (one workgroup per CU); otherwise 128x128 / 2 stages, two workgroups per CU.
+    const long tiles = (long)((M + 255) / 256) * (N / 192), rounds = (tiles + 255) / 256;
     if (tiles >= 160 && 100 * tiles >= (rounds == 1 ? 74 : 90) * rounds * 256) return 7;
   }
   // at most one 128x128 tile per CU: three stages and two k-groups of wavefronts per tile (eight wavefronts on
-  // the CU instead of four) keep more loads in flight.  Long k-loops (FFN2: 35 -> 32 us), and short ones as
-  // well: the 4096 x 768 x 768 problems of the attention projection, whole steps on the BERT-base shape
-  // 0.3835 -> 0.3756 ms (four stages, or one k-group with three stages: 0.379 / 0.380).  With more tiles than
-  // CUs the two-workgroups-per-CU variant is ahead (speech shape, 378 tiles: 0.765 against 0.835 ms).
-  if ((long)((M + 127) / 128) * ((N + 127) / 128) <= 256) return 9;
+  // the CU instead of four) keep more loads in flight.
+  if (b_kc && tiles128 <= 256) return 9;
   return one_round_96 ? 11 : 0;
+}
+}  // namespace
+
+int gemm_pipe_pick_variant(bool a_kc, bool b_kc, int M, int N, int K, bool alone, bool drop) {
+  const int forced = forced_gemm_pipe_variant();
+  if (forced != -1) return forced >= 7 && forced != 8 && forced != 9 && !a_kc ? -2 : forced;
+  if (!a_kc) return b_kc ? -2 : 0;
+  const int base = pipe_base_variant(b_kc, M, N, alone);
+  // Another variant where the time model says that it is clearly ahead: 16384 x 4096 x 1024 on 256x256 tiles 158 -> 141
+  // us, 12608 x 3072 x 768 on 160x128 79 -> 74, 4096 x 3072 x 768 with a k-major B on 256x192 29 -> 24.
+  const int all[6] = {0, 5, 7, 9, 10, 11};
+  int best = drop && !gemm_pipe_takes_dropout(base) ? 0 : base;
+  double best_us = pipe_time(best, M, N, K) * (alone ? 0.95 : 0.90);
+  for (int v : all) {
+    if (drop && !gemm_pipe_takes_dropout(v)) continue;
+    if (!alone && v == 11) continue;
+    const double us = pipe_time(v, M, N, K);
+    if (us < best_us) best_us = us, best = v;
+  }
+  return best;
 }
 
 hipError_t launch_gemm_bf16_pipe(const GemmArgs &a, const void *dev, int splits, int variant, hipStream_t s) {
