@@ -291,54 +291,38 @@ hipError_t launch_attention_fwd(int dt, const void *qkv, const int32_t *lengths,
   return hipGetLastError();
 }
 
-bool attention_bwd_parts_independent(int dt, int dh) {
-  if (forced_general_attention()) return true;
-  return !(dt == DT_BF16 ? attention_mfma_supported(dh) : attention_mfma_f32_supported(dh));
-}
-
 hipError_t launch_attention_bwd(int dt, const void *qkv, const void *o, const void *do_, const float *lse,
                                 const int32_t *lengths, int causal, const DropSpec &drop, int B, int T, int H, int dh,
-                                void *dqkv, float *delta, hipStream_t stream, int parts) {
-  if (!qkv || !o || !do_ || !lse || !dqkv || !delta || !attn_shape_ok(B, T, H, dh) || !(parts & ATTN_BWD_ALL))
-    return hipErrorInvalidValue;
-  if (!attention_bwd_parts_independent(dt, dh)) {  // matrix cores: delta is produced by the dQ kernel
-    if (!(parts & (ATTN_BWD_DQ | ATTN_BWD_DKV))) return hipSuccess;
-    if (dt == DT_F32)
-      return launch_attention_bwd_mfma_f32(qkv, o, do_, lse, lengths, causal, drop, B, T, H, dh, dqkv, delta, stream,
-                                           parts);
-    return launch_attention_bwd_mfma(qkv, o, do_, lse, lengths, causal, drop, B, T, H, dh, dqkv, delta, stream, parts);
-  }
-  if (parts & ATTN_BWD_DELTA) {
-    const int rows = B * T;
-    dim3 grid((rows + 3) / 4), block(256);
-    if (dt == DT_F32)
-      hipLaunchKernelGGL(attn_delta_rows<float>, grid, block, 0, stream, static_cast<const float *>(o),
-                         static_cast<const float *>(do_), rows, T, H, dh, delta);
-    else
-      hipLaunchKernelGGL(attn_delta_rows<bf16_t>, grid, block, 0, stream, static_cast<const bf16_t *>(o),
-                         static_cast<const bf16_t *>(do_), rows, T, H, dh, delta);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (!(parts & (ATTN_BWD_DQ | ATTN_BWD_DKV))) return hipSuccess;
+                                void *dqkv, float *delta, hipStream_t stream) {
+  if (!qkv || !o || !do_ || !lse || !dqkv || !delta || !attn_shape_ok(B, T, H, dh)) return hipErrorInvalidValue;
+  if (dt == DT_F32 && !forced_general_attention() && attention_mfma_f32_supported(dh))
+    return launch_attention_bwd_mfma_f32(qkv, o, do_, lse, lengths, causal, drop, B, T, H, dh, dqkv, delta, stream);
+  if (dt == DT_BF16 && !forced_general_attention() && attention_mfma_supported(dh))
+    return launch_attention_bwd_mfma(qkv, o, do_, lse, lengths, causal, drop, B, T, H, dh, dqkv, delta, stream);
+  const int rows = B * T;
+  dim3 dgrid((rows + 3) / 4);
+  if (dt == DT_F32)
+    hipLaunchKernelGGL(attn_delta_rows<float>, dgrid, dim3(256), 0, stream, static_cast<const float *>(o),
+                       static_cast<const float *>(do_), rows, T, H, dh, delta);
+  else
+    hipLaunchKernelGGL(attn_delta_rows<bf16_t>, dgrid, dim3(256), 0, stream, static_cast<const bf16_t *>(o),
+                       static_cast<const bf16_t *>(do_), rows, T, H, dh, delta);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   const float scale = 1.0f / sqrtf((float)dh);
   dim3 grid((T + ROWS_PER_WG - 1) / ROWS_PER_WG, H, B), block(256);
   if (dt == DT_F32) {
-    if (parts & ATTN_BWD_DQ)
-      hipLaunchKernelGGL(attn_bwd_dq_rows<float>, grid, block, 0, stream, static_cast<const float *>(qkv),
+    hipLaunchKernelGGL(attn_bwd_dq_rows<float>, grid, block, 0, stream, static_cast<const float *>(qkv),
                          static_cast<const float *>(o), static_cast<const float *>(do_), lse, lengths, causal, drop, T,
                          H, dh, scale, static_cast<float *>(dqkv), delta);
-    if (parts & ATTN_BWD_DKV)
-      hipLaunchKernelGGL(attn_bwd_dkv_rows<float>, grid, block, 0, stream, static_cast<const float *>(qkv),
+    hipLaunchKernelGGL(attn_bwd_dkv_rows<float>, grid, block, 0, stream, static_cast<const float *>(qkv),
                          static_cast<const float *>(do_), lse, delta, lengths, causal, drop, T, H, dh, scale,
                          static_cast<float *>(dqkv));
   } else {
-    if (parts & ATTN_BWD_DQ)
-      hipLaunchKernelGGL(attn_bwd_dq_rows<bf16_t>, grid, block, 0, stream, static_cast<const bf16_t *>(qkv),
+    hipLaunchKernelGGL(attn_bwd_dq_rows<bf16_t>, grid, block, 0, stream, static_cast<const bf16_t *>(qkv),
                          static_cast<const bf16_t *>(o), static_cast<const bf16_t *>(do_), lse, lengths, causal, drop,
                          T, H, dh, scale, static_cast<bf16_t *>(dqkv), delta);
-    if (parts & ATTN_BWD_DKV)
-      hipLaunchKernelGGL(attn_bwd_dkv_rows<bf16_t>, grid, block, 0, stream, static_cast<const bf16_t *>(qkv),
+    hipLaunchKernelGGL(attn_bwd_dkv_rows<bf16_t>, grid, block, 0, stream, static_cast<const bf16_t *>(qkv),
                          static_cast<const bf16_t *>(do_), lse, delta, lengths, causal, drop, T, H, dh, scale,
                          static_cast<bf16_t *>(dqkv));
   }

@@ -166,8 +166,13 @@ __device__ __forceinline__ int acc_row(int r, int h) { return (r >> 2) * 8 + h *
 // T = 1000: 150 -> 99 us).
 // dK and dV in one pass up to head size 192 (rolled, that fits the register file); above, two passes.
 constexpr bool dkv_two_passes(int dh) { return dh > 192; }
-// key groups of the forward kernel (see attn_fwd_mfma): large heads, where one group leaves one wavefront per SIMD
-constexpr int fwd_key_groups(int dh, bool drop) { return dh > 128 && dh <= 192 ? 2 : 1; }   // head size 256 does not fit 256 registers
+// Key groups of the forward kernel (see attn_fwd_mfma): two for large heads, where one group leaves one wavefront per
+// SIMD (head size 256 does not fit 256 registers), and for long sequences of 64-wide heads that have too few workgroups
+// to fill the SIMDs with wavefronts of one group each (2 x 900 tokens, 4 heads, causal: 20.5 -> 17.1 us; 4 x 1024, 16
+// heads: 35 -> 33; with 1152 workgroups 46 -> 53, and short sequences only pay for the merge).
+int fwd_key_groups(int dh, int B, int T, int H) {
+  return dh == 192 || (dh == 64 && T > 256 && (long)B * H * ((T + ROWS_WG - 1) / ROWS_WG) <= 512) ? 2 : 1;
+}
 constexpr int fwd_waves(int dh, bool drop) { return dh <= 64 ? (drop ? 3 : 4) : dh <= 128 ? 2 : 1; }
 constexpr int dq_waves(int dh, bool drop) { return dh <= 64 ? (drop ? 2 : 3) : dh <= 96 ? 2 : dh <= 128 ? (drop ? 1 : 2) : 1; }
 constexpr int dkv_waves(int dh) { return dh <= 64 ? 2 : 1; }
@@ -199,7 +204,7 @@ __global__ __launch_bounds__(NT * KG, KG > 1 ? 1 : fwd_waves(DH, DROP)) void att
   bf16_t *const smem = reinterpret_cast<bf16_t *>(smem_raw);
   const int lane = threadIdx.x & 63, h2 = lane >> 5;
   const int wave = (threadIdx.x >> 6) % 4, kgrp = (threadIdx.x >> 6) / 4;   // position among the query rows, key block
-  const AttnBlock blk = attn_block();
+  const AttnBlock blk = attn_block<CAUSAL>();
   const int b = blk.b, hd = blk.hd, rb = blk.rb;
   const int D = H * dh;
   const size_t ld = (size_t)3 * D;
@@ -415,7 +420,7 @@ __global__ __launch_bounds__(NT, dq_waves(DH, DROP)) void attn_bwd_dq_mfma(const
   constexpr int TBATCH = DH <= 64 ? 1 : NB % 2 == 0 ? 2 : 3;   // K^T fragment pairs of a batch
   static_assert(NK % KBATCH == 0 && NB % TBATCH == 0, "batches must divide the head size");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h2 = lane >> 5;
-  const AttnBlock blk = attn_block();
+  const AttnBlock blk = attn_block<CAUSAL>();
   const int b = blk.b, hd = blk.hd, rb = blk.rb;
   const int D = H * dh;
   const size_t ld = (size_t)3 * D;
@@ -572,7 +577,7 @@ __global__ __launch_bounds__(NT, dkv_waves(DH)) void attn_bwd_dkv_mfma(const bf1
   constexpr int TBATCH = DH <= 64 ? 1 : (NB % 3 == 0 && DH < 192) ? 3 : 2;   // transposed dO / Q fragment pairs in flight
   static_assert(NK % KBATCH == 0 && NB % TBATCH == 0, "batches must divide the head size");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h2 = lane >> 5;
-  const AttnBlock blk = attn_block();
+  const AttnBlock blk = attn_block<CAUSAL>();
   const int b = blk.b, hd = blk.hd, rb = blk.rb;
   const int D = H * dh;
   const size_t ld = (size_t)3 * D;
@@ -756,11 +761,10 @@ template <int DH> size_t dkv_lds_bytes() {
   return (size_t)2 * TILE * (kc_stride(DH) + tr_stride(DH)) * sizeof(bf16_t) + 2 * TILE * sizeof(float);
 }
 
-template <int DH, bool CAUSAL, bool DROP>
-hipError_t fwd_t(const void *qkv, const int32_t *lengths, const DropSpec &drop, int B, int T, int H, int dh, float scale,
+template <int DH, bool CAUSAL, bool DROP, int KG>
+hipError_t fwd_k(const void *qkv, const int32_t *lengths, const DropSpec &drop, int B, int T, int H, int dh, float scale,
                  void *o, float *lse, hipStream_t s) {
   dim3 grid((T + ROWS_WG - 1) / ROWS_WG, H, B);
-  constexpr int KG = fwd_key_groups(DH, DROP);
   constexpr size_t lds = (size_t)(KG > 1 ? 2 : 1) * TILE * (kc_stride(DH) + tr_stride(DH)) * sizeof(bf16_t);
   static_assert(lds <= 160 * 1024, "the tiles fit in LDS");
   if (lds > 64 * 1024) {
@@ -775,6 +779,14 @@ hipError_t fwd_t(const void *qkv, const int32_t *lengths, const DropSpec &drop, 
   hipLaunchKernelGGL((attn_fwd_mfma<DH, CAUSAL, DROP, KG>), grid, dim3(NT * KG), lds, s, static_cast<const bf16_t *>(qkv),
                      lengths, drop, T, H, dh, scale, static_cast<bf16_t *>(o), lse);
   return hipGetLastError();
+}
+
+template <int DH, bool CAUSAL, bool DROP>
+hipError_t fwd_t(const void *qkv, const int32_t *lengths, const DropSpec &drop, int B, int T, int H, int dh, float scale,
+                 void *o, float *lse, hipStream_t s) {
+  if constexpr (DH == 64 || DH == 192)
+    if (fwd_key_groups(DH, B, T, H) == 2) return fwd_k<DH, CAUSAL, DROP, 2>(qkv, lengths, drop, B, T, H, dh, scale, o, lse, s);
+  if constexpr (DH != 192) return fwd_k<DH, CAUSAL, DROP, 1>(qkv, lengths, drop, B, T, H, dh, scale, o, lse, s);
 }
 
 template <int DH, int MODE, bool CAUSAL, bool DROP>
@@ -798,17 +810,13 @@ hipError_t launch_dkv(dim3 grid, size_t lds, const void *qkv, const void *dout, 
 
 template <int DH, bool CAUSAL, bool DROP>
 hipError_t bwd_t(const void *qkv, const void *o, const void *dout, const float *lse, const int32_t *lengths,
-                 const DropSpec &drop, int B, int T, int H, int dh, float scale, void *dqkv, float *delta, hipStream_t s, int parts) {
+                 const DropSpec &drop, int B, int T, int H, int dh, float scale, void *dqkv, float *delta, hipStream_t s) {
   dim3 grid((T + ROWS_WG - 1) / ROWS_WG, H, B);
-  hipError_t e = hipSuccess;
-  if (parts & ATTN_BWD_DQ) {
-    hipLaunchKernelGGL((attn_bwd_dq_mfma<DH, CAUSAL, DROP>), grid, dim3(NT), 0, s, static_cast<const bf16_t *>(qkv),
-                       static_cast<const bf16_t *>(o), static_cast<const bf16_t *>(dout), lse, lengths, drop, T, H,
-                       dh, scale, static_cast<bf16_t *>(dqkv), delta);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (!(parts & ATTN_BWD_DKV)) return e;
+  hipLaunchKernelGGL((attn_bwd_dq_mfma<DH, CAUSAL, DROP>), grid, dim3(NT), 0, s, static_cast<const bf16_t *>(qkv),
+                     static_cast<const bf16_t *>(o), static_cast<const bf16_t *>(dout), lse, lengths, drop, T, H,
+                     dh, scale, static_cast<bf16_t *>(dqkv), delta);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   const size_t lds = dkv_lds_bytes<DH>();
   e = launch_dkv<DH, dkv_two_passes(DH) ? 1 : 0, CAUSAL, DROP>(grid, lds, qkv, dout, lse, delta, lengths, drop, T, H, dh, scale, dqkv,
                                                       s);
@@ -828,12 +836,12 @@ hipError_t fwd_pick(int causal, const void *qkv, const int32_t *lengths, const D
 template <int DH>
 hipError_t bwd_pick(int causal, const void *qkv, const void *o, const void *dout, const float *lse,
                     const int32_t *lengths, const DropSpec &drop, int B, int T, int H, int dh, float scale, void *dqkv,
-                    float *delta, hipStream_t s, int parts) {
+                    float *delta, hipStream_t s) {
   if (causal)
-    return drop.thr ? bwd_t<DH, true, true>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts)
-                    : bwd_t<DH, true, false>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
-  return drop.thr ? bwd_t<DH, false, true>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts)
-                  : bwd_t<DH, false, false>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
+    return drop.thr ? bwd_t<DH, true, true>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s)
+                    : bwd_t<DH, true, false>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+  return drop.thr ? bwd_t<DH, false, true>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s)
+                  : bwd_t<DH, false, false>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
 }
 
 }  // namespace
@@ -862,18 +870,18 @@ hipError_t launch_attention_fwd_mfma(const void *qkv, const int32_t *lengths, in
 
 hipError_t launch_attention_bwd_mfma(const void *qkv, const void *o, const void *dout, const float *lse,
                                      const int32_t *lengths, int causal, const DropSpec &drop, int B, int T, int H,
-                                     int dh, void *dqkv, float *delta, hipStream_t s, int parts) {
+                                     int dh, void *dqkv, float *delta, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)dh);
   if (!attention_mfma_supported(dh)) return hipErrorInvalidValue;
-  if ((parts & (ATTN_BWD_DQ | ATTN_BWD_DKV)) == (ATTN_BWD_DQ | ATTN_BWD_DKV) && attention_bwd_fused_applies(T, dh))
+  if (attention_bwd_fused_applies(T, dh))
     return launch_attention_bwd_fused(qkv, o, dout, lse, lengths, causal, drop, B, T, H, dh, dqkv, s);
   switch (instance_of(dh)) {
-    case 32: return bwd_pick<32>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
-    case 64: return bwd_pick<64>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
-    case 96: return bwd_pick<96>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
-    case 128: return bwd_pick<128>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
-    case 192: return bwd_pick<192>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
-    case 256: return bwd_pick<256>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
+    case 32: return bwd_pick<32>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+    case 64: return bwd_pick<64>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+    case 96: return bwd_pick<96>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+    case 128: return bwd_pick<128>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+    case 192: return bwd_pick<192>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+    case 256: return bwd_pick<256>(causal, qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
   }
   return hipErrorInvalidValue;
 }

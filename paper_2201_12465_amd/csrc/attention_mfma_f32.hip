@@ -137,7 +137,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_mfma_f32(const float *__restrict_
   float *const sK = smem, *const sV = smem + TILE * ST;
   const int lane = threadIdx.x & 63, h2 = lane >> 5, l32 = lane & 31;
   const WavePos<KG> wave;
-  const AttnBlock blk = attn_block();
+  const AttnBlock blk = attn_block<CAUSAL>();
   const int b = blk.b, hd = blk.hd, rb = blk.rb;
   const int D = H * dh;
   const size_t ld = (size_t)3 * D;
@@ -265,19 +265,15 @@ __global__ __launch_bounds__(NT) void attn_fwd_mfma_f32(const float *__restrict_
 }
 
 // ------------------------------------------------------------------------------------------ dQ (+ delta)
-template <int DH, bool CAUSAL, bool DROP, int KG>
-__global__ __launch_bounds__(NT) void attn_bwd_dq_mfma_f32(const float *__restrict__ qkv, const float *__restrict__ o,
-                                                           const float *__restrict__ dout,
-                                                           const float *__restrict__ lse,
-                                                           const int32_t *__restrict__ lengths, DropSpec drop, int Tn,
-                                                           int H, int dh, float scale, float *__restrict__ dqkv,
-                                                           float *__restrict__ delta) {
+template <int DH, bool CAUSAL, bool DROP, int KG, bool WRITE_DELTA>
+__device__ __forceinline__ void dq_block(const AttnBlock blk, float *const smem, const float *__restrict__ qkv,
+                                         const float *__restrict__ o, const float *__restrict__ dout,
+                                         const float *__restrict__ lse, const int32_t *__restrict__ lengths, const DropSpec &drop,
+                                         int Tn, int H, int dh, float scale, float *__restrict__ dqkv, float *__restrict__ delta) {
   constexpr int TILE = tile_rows(DH, KG), ST = row_stride(DH), NB = DH / 32, ROWS_WG = rows_wg(KG);
-  extern __shared__ __attribute__((aligned(16))) float smem[];
   float *const sK = smem, *const sV = smem + TILE * ST;
   const int lane = threadIdx.x & 63, h2 = lane >> 5, l32 = lane & 31;
   const WavePos<KG> wave;
-  const AttnBlock blk = attn_block();
   const int b = blk.b, hd = blk.hd, rb = blk.rb;
   const int D = H * dh;
   const size_t ld = (size_t)3 * D;
@@ -298,7 +294,7 @@ __global__ __launch_bounds__(NT) void attn_bwd_dq_mfma_f32(const float *__restri
   dl = half_pair_sum(dl);
   const size_t st_idx = ((size_t)b * H + hd) * Tn + (qok ? q : 0);
   const float L2 = qok ? lse[st_idx] * LOG2E : 0.f;
-  if (qok && h2 == 0 && wave.kg == 0) delta[st_idx] = dl;
+  if (WRITE_DELTA && qok && h2 == 0 && wave.kg == 0) delta[st_idx] = dl;
   const float c = scale * LOG2E;
   f32x16_t acc[NB];
 #pragma unroll
@@ -381,20 +377,17 @@ __global__ __launch_bounds__(NT) void attn_bwd_dq_mfma_f32(const float *__restri
 }
 
 // ------------------------------------------------------------------------------------------ dK, dV
-template <int DH, bool CAUSAL, bool DROP, int KG>
-__global__ __launch_bounds__(NT) void attn_bwd_dkv_mfma_f32(const float *__restrict__ qkv,
-                                                            const float *__restrict__ dout,
-                                                            const float *__restrict__ lse,
-                                                            const float *__restrict__ delta,
-                                                            const int32_t *__restrict__ lengths, DropSpec drop, int Tn,
-                                                            int H, int dh, float scale, float *__restrict__ dqkv) {
+// OWN_DELTA: the queries' delta = dO . O is computed here instead of read.
+template <int DH, bool CAUSAL, bool DROP, int KG, bool OWN_DELTA>
+__device__ __forceinline__ void dkv_block(const AttnBlock blk, float *const smem, const float *__restrict__ qkv,
+                                          const float *__restrict__ o, const float *__restrict__ dout,
+                                          const float *__restrict__ lse, const int32_t *__restrict__ lengths, const DropSpec &drop,
+                                          int Tn, int H, int dh, float scale, float *__restrict__ dqkv, const float *__restrict__ delta) {
   constexpr int TILE = tile_rows(DH, KG), ST = row_stride(DH), NB = DH / 32, ROWS_WG = rows_wg(KG);
-  extern __shared__ __attribute__((aligned(16))) float smem[];
   float *const sQ = smem, *const sDO = smem + TILE * ST;
   float *const sL = sDO + TILE * ST, *const sDl = sL + TILE;   // lse*log2(e) and delta of the tile's queries
   const int lane = threadIdx.x & 63, h2 = lane >> 5, l32 = lane & 31;
   const WavePos<KG> wave;
-  const AttnBlock blk = attn_block();
   const int b = blk.b, hd = blk.hd, rb = blk.rb;
   const int D = H * dh;
   const size_t ld = (size_t)3 * D;
@@ -417,17 +410,37 @@ __global__ __launch_bounds__(NT) void attn_bwd_dkv_mfma_f32(const float *__restr
   const size_t stat0 = ((size_t)b * H + hd) * Tn;
   const float *dobase = dout + (size_t)b * Tn * D + hd * dh;
 
+  const float *obase = o + (size_t)b * Tn * D + hd * dh;
+
   TileRegsF<DH, KG> tq, tdo;
-  float rl = INFINITY, rd = 0.f;   // this thread's lse / delta entry of the tile (threads < TILE)
+  float rl = INFINITY, rd = 0.f;   // lse and delta of a query of the tile, held by the first of its TPR threads
+  constexpr int TPR = NT / TILE;   // threads that share a query's delta = dO . O
+  const int drow = threadIdx.x / TPR, dpart = threadIdx.x % TPR;
   auto load_tile = [&](int q0) {
     const int nvalid = min(TILE, Tn - q0);
     tq.load(base + (size_t)q0 * ld, ld, nvalid, dh);
     tdo.load(dobase + (size_t)q0 * D, (size_t)D, nvalid, dh);
-    if (threadIdx.x < TILE) {
-      const bool ok = (int)threadIdx.x < nvalid;
-      rl = ok ? lse[stat0 + q0 + threadIdx.x] * LOG2E : INFINITY;   // exp2(-inf) = 0 beyond T
-      rd = ok ? delta[stat0 + q0 + threadIdx.x] : 0.f;
+    const bool ok = drow < nvalid;
+    rl = ok ? lse[stat0 + q0 + drow] * LOG2E : INFINITY;   // exp2(-inf) = 0 beyond T
+    rd = 0.f;
+    if constexpr (!OWN_DELTA) {
+      if (ok) rd = delta[stat0 + q0 + drow];
+      return;
     }
+    if (ok) {
+      const size_t at = (size_t)(q0 + drow) * D;
+#pragma unroll
+      for (int i = 0; i < DH / 4 / TPR; ++i) {
+        const int ch = (dpart + i * TPR) * 4;
+        if (ch < dh) {
+          const float4 x = *reinterpret_cast<const float4 *>(dobase + at + ch), y = *reinterpret_cast<const float4 *>(obase + at + ch);
+          rd += (x.x * y.x + x.y * y.y) + (x.z * y.z + x.w * y.w);
+        }
+      }
+    }
+    rd += dpp_lane<0xB1>(rd);                       // the TPR = 2, 4 or 8 lanes are neighbours
+    if constexpr (TPR >= 4) rd += dpp_lane<0x4E>(rd);
+    if constexpr (TPR >= 8) rd += dpp_lane<0x141>(rd);
   };
   // causal: only queries at or after a key see it
   const int qbeg = CAUSAL ? (int)(rb * ROWS_WG) / TILE * TILE : 0;
@@ -437,9 +450,9 @@ __global__ __launch_bounds__(NT) void attn_bwd_dkv_mfma_f32(const float *__restr
     __syncthreads();
     tq.store(sQ);
     tdo.store(sDO);
-    if (threadIdx.x < TILE) {
-      sL[threadIdx.x] = rl;
-      sDl[threadIdx.x] = rd;
+    if (dpart == 0) {
+      sL[drow] = rl;
+      sDl[drow] = rd;
     }
     __syncthreads();
     if (q0 + TILE < Tn) load_tile(q0 + TILE);
@@ -511,6 +524,42 @@ __global__ __launch_bounds__(NT) void attn_bwd_dkv_mfma_f32(const float *__restr
   }
 }
 
+template <int DH, bool CAUSAL, bool DROP, int KG>
+__global__ __launch_bounds__(NT) void attn_bwd_dq_mfma_f32(const float *__restrict__ qkv, const float *__restrict__ o,
+                                                           const float *__restrict__ dout, const float *__restrict__ lse,
+                                                           const int32_t *__restrict__ lengths, DropSpec drop, int Tn, int H,
+                                                           int dh, float scale, float *__restrict__ dqkv,
+                                                           float *__restrict__ delta) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  dq_block<DH, CAUSAL, DROP, KG, true>(attn_block<CAUSAL>(), smem, qkv, o, dout, lse, lengths, drop, Tn, H, dh, scale, dqkv, delta);
+}
+template <int DH, bool CAUSAL, bool DROP, int KG>
+__global__ __launch_bounds__(NT) void attn_bwd_dkv_mfma_f32(const float *__restrict__ qkv, const float *__restrict__ dout,
+                                                            const float *__restrict__ lse, const float *__restrict__ delta,
+                                                            const int32_t *__restrict__ lengths, DropSpec drop, int Tn, int H,
+                                                            int dh, float scale, float *__restrict__ dqkv) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  dkv_block<DH, CAUSAL, DROP, KG, false>(attn_block<CAUSAL>(), smem, qkv, nullptr, dout, lse, lengths, drop, Tn, H, dh, scale, dqkv, delta);
+}
+// dQ and dK/dV in one launch, for problems whose workgroups all run at once: they only share their inputs (each computes
+// the delta it needs), and side by side they take the time of the longer instead of the sum (8 x 128 tokens, 4 heads of
+// 64: 22.7 -> 14.5 us; with more workgroups than CUs the larger of the two register budgets costs more than that: 4 x
+// 1000, 8 heads of 64: 301 -> 383).  The first nrb_q row blocks of a (batch, head) are dQ's.
+template <int DH, bool CAUSAL, bool DROP, int KG>
+__global__ __launch_bounds__(NT) void attn_bwd_both_mfma_f32(const float *__restrict__ qkv, const float *__restrict__ o,
+                                                             const float *__restrict__ dout, const float *__restrict__ lse,
+                                                             const int32_t *__restrict__ lengths, DropSpec drop, int Tn, int H,
+                                                             int dh, float scale, float *__restrict__ dqkv, int nrb_q) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  AttnBlock blk = attn_block<false>();
+  if (blk.rb < nrb_q) {
+    dq_block<DH, CAUSAL, DROP, KG, false>(blk, smem, qkv, o, dout, lse, lengths, drop, Tn, H, dh, scale, dqkv, nullptr);
+  } else {
+    blk.rb -= nrb_q;
+    dkv_block<DH, CAUSAL, DROP, KG, true>(blk, smem, qkv, o, dout, lse, lengths, drop, Tn, H, dh, scale, dqkv, nullptr);
+  }
+}
+
 // The most wavefronts on one group of rows that an instance takes: beyond, the tiles in flight (registers) spill.
 template <int DH> constexpr int MAX_DQ = DH <= 96 ? 4 : 2;
 template <int DH> constexpr int MAX_DKV = DH <= 64 ? 4 : DH <= 96 ? 2 : 1;
@@ -551,11 +600,11 @@ hipError_t dq_k(const float *qkv, const float *o, const float *dout, const float
                 const DropSpec &drop, int B, int T, int H, int dh, float scale, float *dqkv, float *delta, hipStream_t s) {
   constexpr size_t lds = f32_lds_floats<DH, KG>() * sizeof(float);
   static bool raised = false;
-  hipError_t e = raise_lds(attn_bwd_dq_mfma_f32<DH, CAUSAL, DROP, KG>, lds, raised);
+  auto kern = attn_bwd_dq_mfma_f32<DH, CAUSAL, DROP, KG>;
+  hipError_t e = raise_lds(kern, lds, raised);
   if (e != hipSuccess) return e;
   dim3 grid((T + rows_wg(KG) - 1) / rows_wg(KG), H, B);
-  hipLaunchKernelGGL((attn_bwd_dq_mfma_f32<DH, CAUSAL, DROP, KG>), grid, dim3(NT), lds, s, qkv, o, dout, lse, lengths, drop, T,
-                     H, dh, scale, dqkv, delta);
+  hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, qkv, o, dout, lse, lengths, drop, T, H, dh, scale, dqkv, delta);
   return hipGetLastError();
 }
 template <int DH, bool CAUSAL, bool DROP, int KG>
@@ -563,11 +612,23 @@ hipError_t dkv_k(const float *qkv, const float *dout, const float *lse, const fl
                  const DropSpec &drop, int B, int T, int H, int dh, float scale, float *dqkv, hipStream_t s) {
   constexpr size_t lds = f32_lds_floats<DH, KG>() * sizeof(float);
   static bool raised = false;
-  hipError_t e = raise_lds(attn_bwd_dkv_mfma_f32<DH, CAUSAL, DROP, KG>, lds, raised);
+  auto kern = attn_bwd_dkv_mfma_f32<DH, CAUSAL, DROP, KG>;
+  hipError_t e = raise_lds(kern, lds, raised);
   if (e != hipSuccess) return e;
   dim3 grid((T + rows_wg(KG) - 1) / rows_wg(KG), H, B);
-  hipLaunchKernelGGL((attn_bwd_dkv_mfma_f32<DH, CAUSAL, DROP, KG>), grid, dim3(NT), lds, s, qkv, dout, lse, delta, lengths, drop,
-                     T, H, dh, scale, dqkv);
+  hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, qkv, dout, lse, delta, lengths, drop, T, H, dh, scale, dqkv);
+  return hipGetLastError();
+}
+template <int DH, bool CAUSAL, bool DROP, int KG>
+hipError_t both_k(const float *qkv, const float *o, const float *dout, const float *lse, const int32_t *lengths,
+                  const DropSpec &drop, int B, int T, int H, int dh, float scale, float *dqkv, hipStream_t s) {
+  constexpr size_t lds = f32_lds_floats<DH, KG>() * sizeof(float);
+  static bool raised = false;
+  auto kern = attn_bwd_both_mfma_f32<DH, CAUSAL, DROP, KG>;
+  hipError_t e = raise_lds(kern, lds, raised);
+  if (e != hipSuccess) return e;
+  const int nrb = (T + rows_wg(KG) - 1) / rows_wg(KG);
+  hipLaunchKernelGGL(kern, dim3(2 * nrb, H, B), dim3(NT), lds, s, qkv, o, dout, lse, lengths, drop, T, H, dh, scale, dqkv, nrb);
   return hipGetLastError();
 }
 
@@ -582,23 +643,24 @@ hipError_t fwd_t(const float *qkv, const int32_t *lengths, const DropSpec &drop,
 }
 template <int DH, bool CAUSAL, bool DROP>
 hipError_t bwd_t(const float *qkv, const float *o, const float *dout, const float *lse, const int32_t *lengths,
-                 const DropSpec &drop, int B, int T, int H, int dh, float scale, float *dqkv, float *delta,
-                 hipStream_t s, int parts) {
+                 const DropSpec &drop, int B, int T, int H, int dh, float scale, float *dqkv, float *delta, hipStream_t s) {
   const int kg = key_groups(B, T, H);
-  hipError_t e = hipSuccess;
-  if (parts & ATTN_BWD_DQ) {
-    if (kg == 4 && MAX_DQ<DH> == 4) e = dq_k<DH, CAUSAL, DROP, MAX_DQ<DH>>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
-    else if (kg >= 2) e = dq_k<DH, CAUSAL, DROP, 2>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
-    else e = dq_k<DH, CAUSAL, DROP, 1>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
-    if (e != hipSuccess) return e;
+  if constexpr (DH <= 64) {
+    if (2l * B * H * ((T + rows_wg(kg) - 1) / rows_wg(kg)) <= 256) switch (kg) {
+      case 4: return both_k<DH, CAUSAL, DROP, 4>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, s);
+      case 2: return both_k<DH, CAUSAL, DROP, 2>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, s);
+      default: return both_k<DH, CAUSAL, DROP, 1>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, s);
+    }
   }
-  if (parts & ATTN_BWD_DKV) {
-    constexpr int MAX = MAX_DKV<DH>;
-    if (kg >= MAX) e = dkv_k<DH, CAUSAL, DROP, MAX>(qkv, dout, lse, delta, lengths, drop, B, T, H, dh, scale, dqkv, s);
-    else if (kg == 2) e = dkv_k<DH, CAUSAL, DROP, (MAX > 2 ? 2 : MAX)>(qkv, dout, lse, delta, lengths, drop, B, T, H, dh, scale, dqkv, s);
-    else e = dkv_k<DH, CAUSAL, DROP, 1>(qkv, dout, lse, delta, lengths, drop, B, T, H, dh, scale, dqkv, s);
-  }
-  return e;
+  constexpr int QMAX = MAX_DQ<DH>, KMAX = MAX_DKV<DH>;
+  hipError_t e;
+  if (kg == 4 && QMAX == 4) e = dq_k<DH, CAUSAL, DROP, QMAX>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+  else if (kg >= 2) e = dq_k<DH, CAUSAL, DROP, 2>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+  else e = dq_k<DH, CAUSAL, DROP, 1>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+  if (e != hipSuccess) return e;
+  if (kg >= KMAX) return dkv_k<DH, CAUSAL, DROP, KMAX>(qkv, dout, lse, delta, lengths, drop, B, T, H, dh, scale, dqkv, s);
+  if (kg == 2) return dkv_k<DH, CAUSAL, DROP, (KMAX > 2 ? 2 : KMAX)>(qkv, dout, lse, delta, lengths, drop, B, T, H, dh, scale, dqkv, s);
+  return dkv_k<DH, CAUSAL, DROP, 1>(qkv, dout, lse, delta, lengths, drop, B, T, H, dh, scale, dqkv, s);
 }
 
 template <int DH>
@@ -614,12 +676,12 @@ hipError_t fwd_pick(int causal, const float *qkv, const int32_t *lengths, const 
 template <int DH>
 hipError_t bwd_pick(int causal, const float *qkv, const float *o, const float *dout, const float *lse,
                     const int32_t *lengths, const DropSpec &drop, int B, int T, int H, int dh, float scale,
-                    float *dqkv, float *delta, hipStream_t s, int parts) {
+                    float *dqkv, float *delta, hipStream_t s) {
   if (causal)
-    return drop.thr ? bwd_t<DH, true, true>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts)
-                    : bwd_t<DH, true, false>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
-  return drop.thr ? bwd_t<DH, false, true>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts)
-                  : bwd_t<DH, false, false>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s, parts);
+    return drop.thr ? bwd_t<DH, true, true>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s)
+                    : bwd_t<DH, true, false>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
+  return drop.thr ? bwd_t<DH, false, true>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s)
+                  : bwd_t<DH, false, false>(qkv, o, dout, lse, lengths, drop, B, T, H, dh, scale, dqkv, delta, s);
 }
 
 }  // namespace
@@ -643,17 +705,17 @@ hipError_t launch_attention_fwd_mfma_f32(const void *qkv, const int32_t *lengths
 
 hipError_t launch_attention_bwd_mfma_f32(const void *qkv, const void *o, const void *dout, const float *lse,
                                          const int32_t *lengths, int causal, const DropSpec &drop, int B, int T, int H,
-                                         int dh, void *dqkv, float *delta, hipStream_t s, int parts) {
+                                         int dh, void *dqkv, float *delta, hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)dh);
   const float *x = static_cast<const float *>(qkv), *oo = static_cast<const float *>(o);
   const float *g = static_cast<const float *>(dout);
   float *dx = static_cast<float *>(dqkv);
   if (!attention_mfma_f32_supported(dh)) return hipErrorInvalidValue;
   switch ((dh + 31) / 32) {
-    case 1: return bwd_pick<32>(causal, x, oo, g, lse, lengths, drop, B, T, H, dh, scale, dx, delta, s, parts);
-    case 2: return bwd_pick<64>(causal, x, oo, g, lse, lengths, drop, B, T, H, dh, scale, dx, delta, s, parts);
-    case 3: return bwd_pick<96>(causal, x, oo, g, lse, lengths, drop, B, T, H, dh, scale, dx, delta, s, parts);
-    case 4: return bwd_pick<128>(causal, x, oo, g, lse, lengths, drop, B, T, H, dh, scale, dx, delta, s, parts);
+    case 1: return bwd_pick<32>(causal, x, oo, g, lse, lengths, drop, B, T, H, dh, scale, dx, delta, s);
+    case 2: return bwd_pick<64>(causal, x, oo, g, lse, lengths, drop, B, T, H, dh, scale, dx, delta, s);
+    case 3: return bwd_pick<96>(causal, x, oo, g, lse, lengths, drop, B, T, H, dh, scale, dx, delta, s);
+    case 4: return bwd_pick<128>(causal, x, oo, g, lse, lengths, drop, B, T, H, dh, scale, dx, delta, s);
   }
   return hipErrorInvalidValue;
 }

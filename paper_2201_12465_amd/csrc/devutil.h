@@ -144,13 +144,18 @@ __device__ __forceinline__ int xcd_contiguous_order(int bid, int nb) {
 // of one (batch, head) are neighbours in that order, so they pull its K/V (Q/dO) rows through ONE L2 -- with the
 // grid's own coordinates they land on all eight XCDs, and a sequence of 8 row blocks is fetched from the memory
 // side eight times (speech shape, forward: 186 MB per launch for 49 MB of tensors).
+// With the causal mask a row block's work grows with its position (or shrinks: dK/dV), and the workgroups that an XCD's
+// 32 CUs take in turn would give every CU blocks of one position: whole (batch, head) groups are walked backwards in
+// every other round of 32, so that a CU gets a heavy block with a light one (4 x 1024 tokens, 16 heads of 64: forward
+// 32 -> 28 us, dQ and dK/dV 89 -> 76).
 struct AttnBlock { int rb, hd, b; };
-__device__ __forceinline__ AttnBlock attn_block() {
+template <bool CAUSAL> __device__ __forceinline__ AttnBlock attn_block() {
   const int nrb = gridDim.x, H = gridDim.y;
   const int bid = blockIdx.x + nrb * (blockIdx.y + H * blockIdx.z);
   const int id = xcd_contiguous_order(bid, nrb * H * gridDim.z);
   AttnBlock a;
   a.rb = id % nrb;
+  if (CAUSAL && ((id / nrb * nrb) >> 5 & 1)) a.rb = nrb - 1 - a.rb;
   a.hd = (id / nrb) % H;
   a.b = id / (nrb * H);
   return a;

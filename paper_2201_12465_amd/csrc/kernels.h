@@ -163,17 +163,9 @@ hipError_t launch_attention_fwd(int dt, const void *qkv, const int32_t *lengths,
                                 int B, int T, int H, int dh, void *o, float *lse, hipStream_t stream);
 // Backward: dqkv[B*T, 3D] from do_[B*T, D]; delta is fp32 scratch [B,H,T]
 // (delta_i = sum_d dO_i O_i).  Rows of dk, dv at masked keys are written as 0.
-// `parts` selects the steps: ATTN_BWD_DELTA writes delta, ATTN_BWD_DQ the q slab of dqkv, ATTN_BWD_DKV
-// the k and v slabs (both read delta).  With the general kernels dQ and dK/dV do not depend on each
-// other, so a caller may enqueue them on different streams once ATTN_BWD_DELTA is complete
-// (attention_bwd_parts_independent says whether that holds); on the matrix-core path delta comes out of
-// the dQ kernel and the parts must run in order on one stream.
-enum { ATTN_BWD_DELTA = 1, ATTN_BWD_DQ = 2, ATTN_BWD_DKV = 4, ATTN_BWD_ALL = 7 };
 hipError_t launch_attention_bwd(int dt, const void *qkv, const void *o, const void *do_, const float *lse,
                                 const int32_t *lengths, int causal, const DropSpec &drop, int B, int T, int H, int dh,
-                                void *dqkv, float *delta, hipStream_t stream, int parts = ATTN_BWD_ALL);
-bool attention_bwd_parts_independent(int dt, int dh);
-
+                                void *dqkv, float *delta, hipStream_t stream);
 
 // bf16 attention on the matrix cores (attention_mfma.hip); the launchers above pick it when dt is
 // bf16 and the head size is at most 256 (multiples of 16), unless the general kernels are forced.
@@ -182,25 +174,24 @@ hipError_t launch_attention_fwd_mfma(const void *qkv, const int32_t *lengths, in
                                      int T, int H, int dh, void *o, float *lse, hipStream_t s);
 hipError_t launch_attention_bwd_mfma(const void *qkv, const void *o, const void *dout, const float *lse,
                                      const int32_t *lengths, int causal, const DropSpec &drop, int B, int T, int H,
-                                     int dh, void *dqkv, float *delta, hipStream_t s, int parts);
+                                     int dh, void *dqkv, float *delta, hipStream_t s);
 
 // bf16 attention backward in one kernel (attention_bwd_fused.hip): head size 64 and T <= 224, where a
-// (sequence, head) pair fits one workgroup's LDS.  launch_attention_bwd_mfma hands it every such problem
-// whose dQ and dK/dV parts are requested together; delta stays inside the kernel.
+// (sequence, head) pair fits one workgroup's LDS.  launch_attention_bwd_mfma hands it every such problem;
+// delta stays inside the kernel.
 bool attention_bwd_fused_applies(int T, int dh);
 hipError_t launch_attention_bwd_fused(const void *qkv, const void *o, const void *dout, const float *lse,
                                       const int32_t *lengths, int causal, const DropSpec &drop, int B, int T, int H,
                                       int dh, void *dqkv, hipStream_t s);
 
 // fp32 attention on the matrix cores (attention_mfma_f32.hip), picked for dt fp32 and head sizes up
-// to 128 (multiples of 16) unless the general kernels are forced.  As on the bf16 path, delta comes out of the
-// dQ kernel: ATTN_BWD_DQ before ATTN_BWD_DKV on one stream.
+// to 128 (multiples of 16) unless the general kernels are forced.
 bool attention_mfma_f32_supported(int dh);
 hipError_t launch_attention_fwd_mfma_f32(const void *qkv, const int32_t *lengths, int causal, const DropSpec &drop,
                                          int B, int T, int H, int dh, void *o, float *lse, hipStream_t s);
 hipError_t launch_attention_bwd_mfma_f32(const void *qkv, const void *o, const void *dout, const float *lse,
                                          const int32_t *lengths, int causal, const DropSpec &drop, int B, int T, int H,
-                                         int dh, void *dqkv, float *delta, hipStream_t s, int parts);
+                                         int dh, void *dqkv, float *delta, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // dst[j] [cols, rows] = transpose of src[j] [rows, cols] (row-major bf16; rows, cols multiples of 8;

@@ -616,7 +616,7 @@ int attention_backward(void *ctx, Tape *tape, const Node *n) {
   const DropSpec drop = make_drop_spec(L->rec_p_attn, L->rec_seed, 1);
   hipError_t he = timed(FL_K_ATTN_BWD, fl, by, st, [&] {
     return launch_attention_bwd(L->dt, qs.value, os.value, os.grad, static_cast<const float *>(n->s0), L->lengths, L->cfg.causal,
-                                drop, L->B, L->T, H, dh, nb->ptr, delta.f32(), st, ATTN_BWD_ALL);
+                                drop, L->B, L->T, H, dh, nb->ptr, delta.f32(), st);
   });
   if (he != hipSuccess) {
     buf_unref(nb);

@@ -445,6 +445,8 @@ ATTN_CASES = [  # B, T, H, dh, lengths
     (2, 64, 2, 192, [64, 33]),    # exactly one tile; one key for the second group
     (1, 130, 1, 160, [97]),       # padded instance, an odd number of tiles
     (2, 257, 1, 192, [257, 128]), # a last tile of one key; a length on a tile boundary
+    (1, 257, 2, 64, [70]),        # head size 64 past 256 tokens: two key groups as well
+    (2, 321, 1, 64, [321, 33]),
 ]
 
 
