@@ -225,13 +225,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bwd_fused64(const bf16_t *__r
       // pinned: otherwise the reads sink behind the `live` test, one LDS round trip per branch
       asm volatile("" : "+v"(l4.x), "+v"(l4.y), "+v"(l4.z), "+v"(l4.w), "+v"(d4.x), "+v"(d4.y), "+v"(d4.z), "+v"(d4.w));
       const float lq[4] = {l4.x, l4.y, l4.z, l4.w}, dq[4] = {d4.x, d4.y, d4.z, d4.w};
+      float kp[4];
+      if constexpr (DROP) drop_keep_rows4(drop, (uint32_t)key, (uint32_t)(qb * 32 + g * 8 + h2 * 4), (uint32_t)(b * H + hd), kp);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = g * 4 + e, qi = qb * 32 + g * 8 + h2 * 4 + e;
         const float ex = exp2_raw(s[r] * c - lq[e]);
         const float p = (live && (!CAUSAL || qi >= key)) ? ex : 0.f;
         float keep = 1.f;
-        if constexpr (DROP) keep = drop_keep1(drop, (uint32_t)key, (uint32_t)qi, (uint32_t)(b * H + hd));
+        if constexpr (DROP) keep = kp[e];
         dp[r] = p * (dp[r] * keep - dq[e]);   // dS
         s[r] = p * keep;                      // dV sees the dropped-out probabilities
       }

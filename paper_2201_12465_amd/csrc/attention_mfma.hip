@@ -708,13 +708,15 @@ __global__ __launch_bounds__(NT, dkv_waves(DH)) void attn_bwd_dkv_mfma(const bf1
             dq[e] = sDl[qb * 32 + g * 8 + h2 * 4 + e];
           }
         }
+        float kp[4];
+        if constexpr (DROP) drop_keep_rows4(drop, (uint32_t)key, (uint32_t)(q0 + qb * 32 + g * 8 + h2 * 4), (uint32_t)(b * H + hd), kp);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = g * 4 + e, qi = qb * 32 + acc_row(r, h2);
           const float ex = exp2_raw(s[r] * c - lq[e]);
           const float p = (live && (!CAUSAL || q0 + qi >= key)) ? ex : 0.f;
-          float keep = 1.f;   // this lane's key against sixteen different queries: one generator call each
-          if constexpr (DROP) keep = drop_keep1(drop, (uint32_t)key, (uint32_t)(q0 + qi), (uint32_t)(b * H + hd));
+          float keep = 1.f;
+          if constexpr (DROP) keep = kp[e];
           if constexpr (DO_DK) dp[r] = p * (dp[r] * keep - dq[e]);   // dS
           s[r] = p * keep;   // dV sees the dropped-out probabilities
         }

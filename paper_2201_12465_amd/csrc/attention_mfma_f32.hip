@@ -465,12 +465,18 @@ __device__ __forceinline__ void dkv_block(const AttnBlock blk, float *const smem
       zero16(dp);
       s = row_dot<DH>(sQ + (qb * 32 + l32) * ST + h2 * 4, kf, s);      // S[q, key]
       dp = row_dot<DH>(sDO + (qb * 32 + l32) * ST + h2 * 4, vf, dp);   // dP[q, key]
+      float kp[4][4];
+      if constexpr (DROP) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          drop_keep_rows4(drop, (uint32_t)key, (uint32_t)(q0 + qb * 32 + g * 8 + h2 * 4), (uint32_t)(b * H + hd), kp[g]);
+      }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int qi = qb * 32 + acc_row(r, h2);
         const float p = (live && (!CAUSAL || q0 + qi >= key)) ? exp2f(s[r] * c - sL[qi]) : 0.f;
-        float keep = 1.f;   // this lane's key against sixteen different queries: one generator call each
-        if constexpr (DROP) keep = drop_keep1(drop, (uint32_t)key, (uint32_t)(q0 + qi), (uint32_t)(b * H + hd));
+        float keep = 1.f;
+        if constexpr (DROP) keep = kp[r >> 2][r & 3];
         dp[r] = p * (dp[r] * keep - sDl[qi]);   // dS
         s[r] = p * keep;                        // dV sees the dropped-out probabilities
       }

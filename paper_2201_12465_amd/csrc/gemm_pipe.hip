@@ -269,7 +269,7 @@ hipError_t launch_cfg(const GemmDev &d, int splits, hipStream_t s) {
   constexpr bool specialised = (BM == 128 && BN == 128 && WM == 2 && WN == 2 && ((NS == 2 && KG == 1) || (NS == 3 && KG == 2))) ||
                                (BM == 256 && BN == 192) || (BN == 128 && (BM == 160 || BM == 96)) || (BM == 256 && BN == 256 && WN == 4);
   if (d.drop_where) {   // (see gemm_pipe_takes_dropout)
-    if constexpr (AKC && specialised && BM <= 160) return launch_kind<AKC, BKC, BM, BN, NS, WM, WN, KG, true>(d, splits, s);
+    if constexpr (AKC && specialised && (BM <= 160 || BN == 192)) return launch_kind<AKC, BKC, BM, BN, NS, WM, WN, KG, true>(d, splits, s);
     else return hipErrorInvalidValue;
   }
   if constexpr (specialised) return launch_kind<AKC, BKC, BM, BN, NS, WM, WN, KG, false>(d, splits, s);
@@ -317,7 +317,7 @@ void gemm_pipe_tile(int variant, int *bm, int *bn) {
 }
 
 // dropout steps in the epilogue: not with the large wavefront tiles, which have no registers for the generator
-bool gemm_pipe_takes_dropout(int variant) { return variant == 0 || variant == 9 || variant == 10 || variant == 11; }
+bool gemm_pipe_takes_dropout(int variant) { return variant == 0 || variant == 7 || variant == 9 || variant == 10 || variant == 11; }
 
 namespace {
 // Time of a launch that has the chip to itself, in us: tiles per CU (of the fullest) x k-tiles x what a CU takes for one

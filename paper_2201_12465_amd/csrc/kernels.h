@@ -150,7 +150,10 @@ hipError_t launch_layernorm_fwd(int dt, const void *x, const void *gamma, const 
 int ln_bwd_parts(int M, int D);
 hipError_t launch_layernorm_bwd(int dt, const void *dy, const void *x, const float *mean, const float *rstd,
                                 const void *gamma, const void *add, int M, int D, void *dx, float *ws,
-                                hipStream_t stream);
+                                hipStream_t stream, void *dxm = nullptr, const DropSpec &drop = DropSpec());
+// dxm: also dxm = dx (as stored) times the keep mask of the hidden-state site in `drop`, and the third sum taken of dxm
+// instead of dx (only where layernorm_bwd_takes_mask).
+bool layernorm_bwd_takes_mask(int D);
 
 // ---------------------------------------------------------------------------
 // Masked scaled-dot-product attention on the fused projection buffer

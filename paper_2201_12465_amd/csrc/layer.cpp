@@ -352,6 +352,7 @@ void release_tape(fl_layer *L, bool host_wait = false) {
   for (Slot &s : L->tape.slots) {
     buf_unref(s.value_buf);
     buf_unref(s.grad_buf);
+    buf_unref(s.masked);
   }
   for (Node &n : L->tape.nodes)
     for (Buf *&b : n.saved) buf_unref(b);
@@ -512,7 +513,11 @@ int linear_backward(void *ctx, Tape *tape, const Node *n) {
   // The linear output was dropped out before it was added to the residual stream: the identity branch
   // (below) passes the sum's gradient on as it is, the linear layer sees it times the keep mask.
   Buf *gm = nullptr;
-  if (n->flags && L->rec_p_hidden > 0.f) {
+  if (n->flags && L->rec_p_hidden > 0.f && ys.masked) {   // the kernel that finished the gradient has left it behind
+    gm = ys.masked;
+    ys.masked = nullptr;
+    gy = gm->ptr;
+  } else if (n->flags && L->rec_p_hidden > 0.f) {
     gm = buf_new((size_t)M * N * e, st);
     if (!gm) return oom_error((size_t)M * N * e);
     hipError_t he = launch_dropout_mul(dt, gy, gm->ptr, M, N, make_drop_spec(L->rec_p_hidden, L->rec_seed, n->flags), st);
@@ -656,17 +661,32 @@ int layernorm_backward(void *ctx, Tape *tape, const Node *n) {
     if (!nb) return oom_error((size_t)M * D * e);
     dst = nb->ptr;
   }
+  // x was dropped out in front of its residual add: its linear layer wants this gradient times the keep mask, too
+  Buf *mb = nullptr;
+  DropSpec drop;
+  if (fin && xs.mask_site && L->rec_p_hidden > 0.f && layernorm_bwd_takes_mask(D)) {
+    mb = buf_new((size_t)M * D * e, st);
+    if (!mb) {
+      buf_unref(nb);
+      return oom_error((size_t)M * D * e);
+    }
+    drop = make_drop_spec(L->rec_p_hidden, L->rec_seed, (uint32_t)xs.mask_site);
+  }
   const float *mean = static_cast<const float *>(n->s0);
-  const double by = (double)M * D * e * (xs.grad ? 4 : 3) + 8.0 * M;
+  const double by = (double)M * D * e * ((xs.grad ? 4 : 3) + (mb ? 1 : 0)) + 8.0 * M;
   hipError_t he = timed(FL_K_LN_BWD, 0, by, st, [&] {
-    return launch_layernorm_bwd(dt, ys.grad, xs.value, mean, mean + M, L->params[gi], xs.grad, M, D, dst, ws.f32(), st);
+    return launch_layernorm_bwd(dt, ys.grad, xs.value, mean, mean + M, L->params[gi], xs.grad, M, D, dst, ws.f32(), st,
+                                mb ? mb->ptr : nullptr, drop);
   });
   if (he != hipSuccess) {
     buf_unref(nb);
+    buf_unref(mb);
     FL_HIP(he);
   }
   set_grad(xs, dst, nb);
-  const bool want_bias = fin && xs.colsum_param >= 0;
+  xs.masked = mb;
+  // the third sum is the bias gradient, unless the bias wants the masked gradient's sums and these are not
+  const bool want_bias = fin && xs.colsum_param >= 0 && (!xs.mask_site || L->rec_p_hidden == 0.f || mb);
   // second stage of the parameter-gradient sums: with the weight gradients at the end of the pass
   hold(L, ws.b);
   FL_TRY(dw_column(L, ws.f32(), parts, 3 * D, D, true, L->grads[gi]));
@@ -732,8 +752,9 @@ int op_linear(fl_layer *L, int lin, int xslot, int rslot, int act, int K, int N,
   s.value = y;
   s.value_buf = yb;
   // the bias gradient is the column sum of the gradient that enters the linear layer: with a dropped-out
-  // output in front of a residual add that is NOT the gradient of this slot (linear_backward masks it first)
-  s.colsum_param = dropped && act == XF_NONE ? -1 : kLinear[lin].b;
+  // output in front of a residual add that is the gradient of this slot times the keep mask
+  s.colsum_param = kLinear[lin].b;
+  if (dropped && act == XF_NONE) s.mask_site = site;
   if (act != XF_NONE) {
     s.xform = act;
     s.xform_aux = act == XF_GELU && ub ? ub->ptr : y;  // ReLU: the output's sign is the pre-activation's

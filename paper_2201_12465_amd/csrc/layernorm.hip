@@ -16,6 +16,7 @@
 // columns never change from row to row.
 #include "devutil.h"
 #include "kernels.h"
+#include "philox.h"
 
 namespace fl {
 namespace {
@@ -231,12 +232,15 @@ __global__ __launch_bounds__((NCH * Elem<T>::VEC > 16) ? 256 : 512) void ln_bwd_
 // workgroup's range, one row per turn.  The raw 16-byte chunks of the next PF rows (dy, x, the skip
 // gradient, and the two row statistics) are requested before the current row is reduced, so that a
 // wavefront always has PF rows in flight while it computes; a lane holds at most 16 elements of a row.
-template <typename T, int NCH, bool ADD>
+// MASK: dx is also written multiplied by the dropout keep mask of the linear layer that produced x (dxm), and the third sum
+// is that of the masked values: they are what that layer's gradients see.
+template <typename T, int NCH, bool ADD, bool MASK>
 __global__ __launch_bounds__(512) void ln_bwd_rows_kernel(const T *__restrict__ dy, const T *__restrict__ x,
                                                           const float *__restrict__ mean,
                                                           const float *__restrict__ rstd, const T *__restrict__ gamma,
                                                           const T *__restrict__ add, int M, int D, int rows_per_wg,
-                                                          T *__restrict__ dx, float *__restrict__ ws) {
+                                                          T *__restrict__ dx, float *__restrict__ ws, T *__restrict__ dxm,
+                                                          DropSpec drop) {
   constexpr int VEC = Elem<T>::VEC;
   constexpr int PF = 3, NW = 8;
   extern __shared__ float red[];  // [NW][3][D]
@@ -322,9 +326,23 @@ __global__ __launch_bounds__(512) void ln_bwd_rows_kernel(const T *__restrict__ 
       for (int e = 0; e < VEC; ++e) {
         o[e] = rs * (d[i][e] * gam[i][e] - a1 - xh[i][e] * a2) + (ADD ? av[i][e] : 0.f);
         if (c >= nchunks) o[e] = 0.f;
-        px[i][e] += o[e];
+        if (!MASK) px[i][e] += o[e];
       }
       if (c < nchunks) VecIO<T, VEC>::store(dx + (size_t)m * D + c * VEC, o);
+      if constexpr (MASK) {
+#pragma unroll
+        for (int g = 0; g < VEC / 4; ++g) {
+          float kp[4];
+          drop_keep4(drop, (uint32_t)(c * (VEC / 4) + g), (uint32_t)m, 0u, kp);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            // the masked copy of what was stored, rounded as stored: the multiplier meets the rounded value
+            o[g * 4 + e] = to_f32(from_f32<T>(o[g * 4 + e])) * kp[e];
+            px[i][g * 4 + e] += o[g * 4 + e];
+          }
+        }
+        if (c < nchunks) VecIO<T, VEC>::store(dxm + (size_t)m * D + c * VEC, o);
+      }
     }
   }
   // fold the waves' partial rows through LDS in one pass: wave w writes its three rows (16-byte pieces:
@@ -379,7 +397,7 @@ hipError_t ln_fwd_t(const void *x, const void *g, const void *b, float eps, int 
 
 template <typename T>
 hipError_t ln_bwd_t(const void *dy, const void *x, const float *mean, const float *rstd, const void *g,
-                    const void *add, int M, int D, void *dx, float *ws, hipStream_t s) {
+                    const void *add, int M, int D, void *dx, float *ws, void *dxm, const DropSpec &drop, hipStream_t s) {
   constexpr int VEC = Elem<T>::VEC;
   const int nch = (D / VEC + 63) / 64;
   const int nw = ln_waves(D);
@@ -387,9 +405,9 @@ hipError_t ln_bwd_t(const void *dy, const void *x, const float *mean, const floa
   const int rows_per_wg = (M + parts - 1) / parts;
   dim3 grid(parts), block(64 * nw);
   const size_t lds = (size_t)nw * D * sizeof(float) * (nch * VEC <= 16 ? 3 : 1);  // the pipelined kernel folds all three sums at once
-#define FL_LN_ROWS(N, A)                                                                                      \
+#define FL_LN_ROWS_M(N, A, K)                                                                                 \
   do {                                                                                                        \
-    auto kern = ln_bwd_rows_kernel<T, N, A>;                                                                  \
+    auto kern = ln_bwd_rows_kernel<T, N, A, K>;                                                                \
     static bool raised = false;                                                                               \
     if (lds > 64 * 1024 && !raised) { /* more dynamic LDS than the default limit: allow the CU's 160 KB */    \
       hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),                                \
@@ -399,12 +417,18 @@ hipError_t ln_bwd_t(const void *dy, const void *x, const float *mean, const floa
     }                                                                                                         \
     hipLaunchKernelGGL(kern, grid, block, lds, s, static_cast<const T *>(dy), static_cast<const T *>(x),      \
                        mean, rstd, static_cast<const T *>(g), static_cast<const T *>(add), M, D, rows_per_wg, \
-                       static_cast<T *>(dx), ws);                                                             \
+                       static_cast<T *>(dx), ws, static_cast<T *>(dxm), drop);                                \
+  } while (0)
+#define FL_LN_ROWS(N, A)                                                                                      \
+  do {                                                                                                        \
+    if (dxm) FL_LN_ROWS_M(N, A, true);                                                                        \
+    else FL_LN_ROWS_M(N, A, false);                                                                           \
   } while (0)
 #define FL_LN_BWD(N)                                                                                          \
   hipLaunchKernelGGL((ln_bwd_kernel<T, N>), grid, block, lds, s, static_cast<const T *>(dy),                  \
                      static_cast<const T *>(x), mean, rstd, static_cast<const T *>(g),                        \
                      static_cast<const T *>(add), M, D, rows_per_wg, static_cast<T *>(dx), ws)
+  if (dxm && nch * VEC > 16) return hipErrorInvalidValue;   // see layernorm_bwd_takes_mask
   if (nch * VEC <= 16) {  // at most 16 elements of a row per lane: the pipelined kernel
     if (nch <= 1) { if (add) FL_LN_ROWS(1, true); else FL_LN_ROWS(1, false); }
     else if (nch <= 2) { if (add) FL_LN_ROWS(2, true); else FL_LN_ROWS(2, false); }
@@ -416,6 +440,7 @@ hipError_t ln_bwd_t(const void *dy, const void *x, const float *mean, const floa
   else return hipErrorInvalidValue;
 #undef FL_LN_BWD
 #undef FL_LN_ROWS
+#undef FL_LN_ROWS_M
   return hipGetLastError();
 }
 
@@ -438,13 +463,15 @@ hipError_t launch_layernorm_fwd(int dt, const void *x, const void *gamma, const 
                       : ln_fwd_t<bf16_t>(x, gamma, beta, eps, M, D, y, mean, rstd, stream);
 }
 
+bool layernorm_bwd_takes_mask(int D) { return D <= 1024; }
+
 hipError_t launch_layernorm_bwd(int dt, const void *dy, const void *x, const float *mean, const float *rstd,
                                 const void *gamma, const void *add, int M, int D, void *dx, float *ws,
-                                hipStream_t stream) {
+                                hipStream_t stream, void *dxm, const DropSpec &drop) {
   if (!dy || !x || !mean || !rstd || !gamma || !dx || !ws || M < 1 || D < 8 || D % 8 || D > 4096)
     return hipErrorInvalidValue;
-  return dt == DT_F32 ? ln_bwd_t<float>(dy, x, mean, rstd, gamma, add, M, D, dx, ws, stream)
-                      : ln_bwd_t<bf16_t>(dy, x, mean, rstd, gamma, add, M, D, dx, ws, stream);
+  return dt == DT_F32 ? ln_bwd_t<float>(dy, x, mean, rstd, gamma, add, M, D, dx, ws, dxm, drop, stream)
+                      : ln_bwd_t<bf16_t>(dy, x, mean, rstd, gamma, add, M, D, dx, ws, dxm, drop, stream);
 }
 
 }  // namespace fl

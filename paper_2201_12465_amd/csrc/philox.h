@@ -43,12 +43,11 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
                                                uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-    c0 = hi1 ^ c1 ^ k0;
-    c1 = lo1;
-    c2 = hi0 ^ c3 ^ k1;
-    c3 = lo0;
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;   // one 64-bit multiply each
+    c0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+    c1 = (uint32_t)p1;
+    c2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    c3 = (uint32_t)p0;
     k0 += 0x9E3779B9u;
     k1 += 0xBB67AE85u;
   }
@@ -68,6 +67,18 @@ __device__ __forceinline__ float drop_keep1(const DropSpec &d, uint32_t n, uint3
   const uint4 w = philox4x32_10(n >> 2, c1, d.site, c3, d.k0, d.k1);
   const uint32_t v = (n & 3) == 0 ? w.x : ((n & 3) == 1 ? w.y : ((n & 3) == 2 ? w.z : w.w));
   return v >= d.thr ? d.scale : 0.f;
+}
+// Multipliers of the elements (rows row0 .. row0+3, column n), for lanes whose columns are consecutive from a multiple of
+// four on: the four lanes of a quad need words of the same four calls, so each makes one of them and hands its four
+// decisions round (a call costs about 280 clocks of the vector ALU, the exchange 100).
+__device__ __forceinline__ void drop_keep_rows4(const DropSpec &d, uint32_t n, uint32_t row0, uint32_t c3, float (&m)[4]) {
+  const uint32_t j = n & 3;
+  const uint4 w = philox4x32_10(n >> 2, row0 + j, d.site, c3, d.k0, d.k1);
+  const int bits = (w.x >= d.thr ? 1 : 0) | (w.y >= d.thr ? 2 : 0) | (w.z >= d.thr ? 4 : 0) | (w.w >= d.thr ? 8 : 0);
+  const int b[4] = {__builtin_amdgcn_update_dpp(0, bits, 0x00, 0xF, 0xF, true), __builtin_amdgcn_update_dpp(0, bits, 0x55, 0xF, 0xF, true),
+                    __builtin_amdgcn_update_dpp(0, bits, 0xAA, 0xF, 0xF, true), __builtin_amdgcn_update_dpp(0, bits, 0xFF, 0xF, 0xF, true)};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) m[e] = (b[e] >> j) & 1 ? d.scale : 0.f;
 }
 #endif
 

@@ -42,7 +42,9 @@ struct Slot {
   const void *xform_aux = nullptr;  // pre-activation (GELU) or activation output (ReLU)
   int32_t colsum_param = -1;        // also emit the gradient's column sums as this bias's gradient
   int32_t xform_drop_site = 0;      // also multiply it by the dropout keep mask of this site (0 = none)
+  int32_t mask_site = 0;            // also leave the gradient times the dropout keep mask of this site in `masked`
   // backward
+  Buf *masked = nullptr;     // set by an operator that has served that request
   void *grad = nullptr;      // gradient accumulated so far (nullptr = none yet)
   Buf *grad_buf = nullptr;   // set if the library owns it
   void *grad_dst = nullptr;  // caller-owned destination the finished gradient must land in
