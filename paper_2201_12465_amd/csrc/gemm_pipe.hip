@@ -95,7 +95,7 @@ __device__ __forceinline__ bf16x8_t frag(const unsigned char *stage, int r0, int
 
 // WM x WN wavefronts share a BM x BN tile; each owns TM x TN MFMA tiles of 32x32.  KG > 1: KG such
 // groups of wavefronts work on the same tile, group g taking the g-th part of every k-tile, and their
-// accumulators are added through LDS at the end.  For outputs with few tiles (one workgroup per CU)
+// accumulators are added through LDS at the end, half of the tile by either group.  For outputs with few tiles (one workgroup per CU)
 // this puts two wavefronts on every SIMD, so that one's LDS reads overlap the other's MFMAs.
 template <bool AKC, bool BKC, int BM, int BN, int NS, int WM, int WN, bool DROP, int KG, int EPI = EPI_FULL>
 __global__ __launch_bounds__(WM *WN *KG * 64) void gemm_bf16_pipe(GemmDev p) {
@@ -195,43 +195,39 @@ __global__ __launch_bounds__(WM *WN *KG * 64) void gemm_bf16_pipe(GemmDev p) {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();  // every wave is done reading the operand stages
   asm volatile("" ::: "memory");
-  if constexpr (KG > 1) {
-    // groups 1.. park their accumulators in LDS ([group-1][position][register][lane]: lane-contiguous,
-    // no bank conflicts), group 0 adds them up and goes on alone
-    float *red = reinterpret_cast<float *>(smem);
-    constexpr int PER_WAVE = TM * TN * 16 * 64;
-    if (kg > 0) {
-      float *dst = red + ((size_t)(kg - 1) * (WM * WN) + wpos) * PER_WAVE + lane;
+  if constexpr (KG == 2) {
+    // each group finishes half of the tile's 32-row blocks: it parks its sums of the other half in LDS ([position][register]
+    // [lane]: lane-contiguous, no bank conflicts), adds the other group's to its own, and both walk the epilogue
+    static_assert(TM == 2, "one block of rows for each group");
+    constexpr int PER_WAVE = TN * 16 * 64;
+    float *red = reinterpret_cast<float *>(smem) + (size_t)wpos * PER_WAVE + lane;
+    float *dst = red + (size_t)kg * (WM * WN) * PER_WAVE;
+    const float *src = red + (size_t)(1 - kg) * (WM * WN) * PER_WAVE;
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) dst[((i * TN + j) * 16 + r) * 64] = acc[i][j][r];
-    }
+      for (int r = 0; r < 16; ++r) dst[(j * 16 + r) * 64] = kg == 0 ? acc[1][j][r] : acc[0][j][r];
     __syncthreads();
+    f32x16_t fin[1][TN];
 #pragma unroll
-    for (int g = 1; g < KG && kg == 0; ++g) {
-      const float *src = red + ((size_t)(g - 1) * (WM * WN) + wpos) * PER_WAVE + lane;
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] += src[((i * TN + j) * 16 + r) * 64];
-    }
+      for (int r = 0; r < 16; ++r) fin[0][j][r] = (kg == 0 ? acc[0][j][r] : acc[1][j][r]) + src[(j * 16 + r) * 64];
     __syncthreads();  // the epilogue's staging area overlaps what other wavefronts have just read
-    if (kg > 0) return;  // no barrier follows: group 0 finishes alone
+    float *cw = reinterpret_cast<float *>(smem) + (size_t)wave * 32 * (TN * 32 + 4);
+    gemm_staged_epilogue<bf16_t, 1, TN, DROP, EPI>(p, fin, cw, row0 + wm * (BM / WM) + kg * 32, col0 + wn * (BN / WN), lane);
+  } else {
+    static_assert(KG == 1, "one or two k-groups");
+    float *cw = reinterpret_cast<float *>(smem) + (size_t)wpos * 32 * (TN * 32 + 4);
+    gemm_staged_epilogue<bf16_t, TM, TN, DROP, EPI>(p, acc, cw, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane);
   }
-  float *cw = reinterpret_cast<float *>(smem) + (size_t)wpos * 32 * (TN * 32 + 4);
-  gemm_staged_epilogue<bf16_t, TM, TN, DROP, EPI>(p, acc, cw, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane);
 }
 
 template <bool AKC, bool BKC, int BM, int BN, int NS, int WM, int WN, bool DROP, int KG, int EPI = EPI_FULL>
 hipError_t launch_cfg_d(GemmDev d, int splits, hipStream_t s) {
   constexpr size_t stage_lds = (size_t)NS * (BM + BN) * 128;
-  constexpr size_t epi_lds = (size_t)WM * WN * 32 * (BN / WN + 4) * sizeof(float);
-  constexpr size_t red_lds = (size_t)(KG - 1) * BM * BN * sizeof(float);
+  constexpr size_t epi_lds = (size_t)WM * WN * KG * 32 * (BN / WN + 4) * sizeof(float);
+  constexpr size_t red_lds = KG > 1 ? (size_t)BM * BN * sizeof(float) : 0;
   constexpr size_t lds0 = stage_lds > epi_lds ? stage_lds : epi_lds;
   constexpr size_t lds = lds0 > red_lds ? lds0 : red_lds;
   static_assert(lds <= 160 * 1024, "stages do not fit in LDS");
