@@ -8,7 +8,7 @@
 // 0.94 us (4.5), 256 x 256 1.41 us (6.0).  Alone on the chip there is no second kernel to leave room for, so the
 // tile and the token split are picked by those rates (dw_plan).
 // A token count that is not a multiple of 64: the last k-tile's rows past the end are fetched from the last token and
-// zeroed in the fragments of gy.
+// zeroed in the fragments of gy and x (0 times an infinity of the last token would be a NaN).
 #include "gemm_dw.h"
 #include "lds_dma.h"
 
@@ -125,7 +125,11 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_dw_pipe(DwDev d) {
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int e = 0; e < 8; ++e)
-            if (kbeg + kt * KT + kk * 16 + (lane >> 5) * 8 + e >= kend) fa[kk & 1][i][e] = (bf16_t)0.f;
+            if (kbeg + kt * KT + kk * 16 + (lane >> 5) * 8 + e >= kend) {
+              fa[kk & 1][i][e] = (bf16_t)0.f;
+#pragma unroll
+              for (int j = 0; j < TN; ++j) fb[kk & 1][j][e] = (bf16_t)0.f;
+            }
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -212,8 +216,7 @@ hipError_t launch_dw_batch(int dt, const DwPlan &plan, const DwJob *jobs, int nj
   if (njobs < 1 || njobs > DW_MAX_JOBS || ncols < 0 || ncols > DW_MAX_COLS || M < 1 || plan.splits < 1) return hipErrorInvalidValue;
   for (int j = 0; j < njobs; ++j) {
     const DwJob &J = jobs[j];
-    if (!J.gy || !J.x || !J.out || (plan.splits > 1 && !J.partial) || J.N < 8 || J.K < 8 || J.N % 8 || J.K % 8 ||
-        (long)M * J.N >= (1l << 31) || (long)M * J.K >= (1l << 31))
+    if (!J.gy || !J.x || !J.out || (plan.splits > 1 && !J.partial) || J.N < 8 || J.K < 8 || J.N % 8 || J.K % 8)
       return hipErrorInvalidValue;
   }
   for (int j = 0; j < ncols; ++j)

@@ -183,6 +183,47 @@ def test_weight_gradient_batch(dtype, kernel, splits, shape):
             assert rel_err(to_np(o), r + (w if accumulate else 0.0)) <= _tol(dtype), accumulate
 
 
+@pytest.mark.parametrize("dtype,kernel", [("bf16", k) for k in range(5)] + [("f32", 3), ("f32", 4)])
+def test_weight_gradients_keep_an_infinity_of_the_last_token(dtype, kernel):
+    """The rows that fill up the last k-tile are copies of the last token: they must not turn its infinity into a NaN."""
+    b = _lib()
+    torch = torch_mod()
+    M, N, K = 67, 136, 72
+    rng = np.random.default_rng(3)
+    gy, x = (np.abs(rng.standard_normal(s)) + 0.5 for s in ((M, N), (M, K)))
+    x[-1, 5], gy[-1, 9] = np.inf, np.inf
+    tgy, tx = to_dev(gy, dtype), to_dev(x, dtype)
+    out = [empty_dev(s, dtype) for s in ((N, K), (K, N), (N,))]
+    part = torch.empty(2 * N * K, device="cuda")
+    b.check(b.lib().fl_test_dw_batch(dt_code(dtype), kernel, 1, 0, tgy.data_ptr(), tx.data_ptr(), M, N, K,
+                                     *[o.data_ptr() for o in out], part.data_ptr(), stream_ptr()))
+    dW, dWt, db = (to_np(o) for o in out)
+    want = np.zeros((N, K), bool)
+    want[:, 5] = want[9, :] = True
+    assert np.array_equal(dW == np.inf, want) and np.array_equal(dWt == np.inf, want.T) and db[9] == np.inf
+    assert not np.isnan(dW).any() and not np.isnan(dWt).any()
+
+
+def test_weight_gradients_of_operands_past_2_31_elements():
+    b = _lib()
+    torch = torch_mod()
+    M, N, K = (1 << 20) + 37, 2056, 8
+    gy = torch.zeros(M, N, dtype=torch.bfloat16, device="cuda")
+    x = torch.zeros(M, K, dtype=torch.bfloat16, device="cuda")
+    rows = [0, 1000003, M - 2, M - 1]
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    for r in rows:
+        gy[r] = torch.randn(N, device="cuda", generator=gen).bfloat16()
+        x[r] = torch.randn(K, device="cuda", generator=gen).bfloat16()
+    out = [empty_dev(s, "bf16") for s in ((N, K), (K, N), (N,))]
+    part = torch.empty(2 * 16 * N * K, device="cuda")
+    b.check(b.lib().fl_test_dw_batch(dt_code("bf16"), -1, 1, 0, gy.data_ptr(), x.data_ptr(), M, N, K,
+                                     *[o.data_ptr() for o in out], part.data_ptr(), stream_ptr()))
+    g, v = to_np(gy[rows]), to_np(x[rows])
+    for o, r in zip(out, (g.T @ v, v.T @ g, g.sum(0))):
+        assert rel_err(to_np(o), r) <= _tol("bf16")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("act", [0, 1, 2])
 def test_gemm_forward_epilogue(dtype, act):
