@@ -871,6 +871,23 @@ int check_ptrs(const void *const *v, int n, const char *what) {
   return 0;
 }
 
+// Everything a backward pass enqueues is on the layer's stream: only another stream has something to wait for.  Where
+// the caller has destroyed the layer's stream since, the host waits instead.
+int join_impl(fl_layer *L, hipStream_t s) {
+  if (!L->join_open) return 0;
+  if (s != L->stream) {
+    if (!L->join_event) FL_HIP(hipEventCreateWithFlags(&L->join_event, kEventFlags));
+    if (hipEventRecord(L->join_event, L->stream) != hipSuccess) {
+      (void)hipGetLastError();
+      FL_HIP(hipDeviceSynchronize());
+    } else {
+      FL_HIP(hipStreamWaitEvent(s, L->join_event, 0));
+    }
+  }
+  L->join_open = false;
+  return 0;
+}
+
 int forward_impl(fl_layer *L, const fl_layer_params_t *params, const void *X, const int32_t *lengths, int B, int T,
                  void *Y, hipStream_t st) {
   const fl_layer_config_t &c = L->cfg;
@@ -890,7 +907,7 @@ int forward_impl(fl_layer *L, const fl_layer_params_t *params, const void *X, co
       if (h[b] < 1 || h[b] > T)
         return set_error(FL_ERR_INVALID_ARG, "lengths[%d] = %d is outside 1..T = %d", b, h[b], T);
   }
-  L->join_open = false;
+  FL_TRY(join_impl(L, st));
   release_tape(L);
   L->B = B; L->T = T; L->M = B * T; L->stream = st; L->lengths = lengths;
   L->rec_p_attn = L->p_attn; L->rec_p_hidden = L->p_hidden; L->rec_seed = L->seed;
@@ -934,8 +951,8 @@ int forward_static_impl(fl_layer *L, const fl_layer_params_t *params, const void
   if (B < 1 || T < 1 || B > c.max_B || T > c.max_T)
     return set_error(FL_ERR_INVALID_ARG, "B=%d T=%d outside 1..max_B=%d, 1..max_T=%d", B, T, c.max_B, c.max_T);
   if ((long)B * T > (1l << 24)) return set_error(FL_ERR_UNSUPPORTED, "B*T too large");
-  if (L->tape.recorded)
-    return set_error(FL_ERR_STATE, "the handle holds a recorded forward: run its backward first");
+  if (L->tape.recorded || (L->join_open && g_overlap && (long)L->M * c.d_model >= (1l << 18)))
+    return set_error(FL_ERR_STATE, "the handle holds a recorded forward or, at this size, an open join: run its backward (and join) first");
   load_params(L, params);
   FL_TRY(check_ptrs(L->params, P_COUNT, "params"));
   const void *io[2] = {X, Y};
@@ -1026,30 +1043,28 @@ int backward_impl(fl_layer *L, const fl_layer_params_t *params, const void *dY, 
   const void *io[2] = {dY, dX};
   FL_TRY(check_ptrs(io, 2, "dY/dX"));
   Tape &tp = L->tape;
+  // A pre-LN layer's last weight gradient reads dY, and it runs at the end of the pass: where dX lies on dY, dX is made
+  // in scratch memory and copied behind that launch.
+  const size_t io_bytes = (size_t)L->M * L->cfg.d_model * esize(L);
+  const char *dy0 = static_cast<const char *>(dY), *dx0 = static_cast<const char *>(dX);
+  Scratch apart;
+  if (L->cfg.norm != FL_NORM_POST && dy0 < dx0 + io_bytes && dx0 < dy0 + io_bytes) FL_TRY(apart.get(io_bytes, st));
+  void *const dst = apart.b ? apart.b->ptr : dX;
   tp.slots[L->slot_y].grad = const_cast<void *>(dY);
-  tp.slots[L->slot_x].grad_dst = dX;
+  tp.slots[L->slot_x].grad_dst = dst;
   dw_drop(L);
   int rc = tp.replay_reverse(L);
   if (!rc) rc = dw_flush(L);
   else dw_drop(L);
-  const bool landed = rc == 0 && tp.slots[L->slot_x].grad == dX;
+  const bool landed = rc == 0 && tp.slots[L->slot_x].grad == dst;
   release_tape(L);
   if (rc) return rc;
+  if (landed && apart.b) FL_HIP(hipMemcpyAsync(dX, dst, io_bytes, hipMemcpyDeviceToDevice, st));
   if (!landed) return set_error(FL_ERR_STATE, "input gradient did not reach its destination");
   L->join_open = L->defer_join;
   return 0;
 }
 
-// Everything a backward pass enqueues is on the layer's stream: only another stream has something to wait for.
-int join_impl(fl_layer *L, hipStream_t s) {
-  if (!L->join_open) return 0;
-  L->join_open = false;
-  if (s == L->stream) return 0;
-  if (!L->join_event) FL_HIP(hipEventCreateWithFlags(&L->join_event, kEventFlags));
-  FL_HIP(hipEventRecord(L->join_event, L->stream));
-  FL_HIP(hipStreamWaitEvent(s, L->join_event, 0));
-  return 0;
-}
 
 }  // namespace
 
@@ -1204,6 +1219,10 @@ fl_status_t fl_zero_grad(fl_dtype_t dtype, int32_t n, void *const *grads, const 
 fl_status_t fl_layer_destroy(fl_layer_t *layer) {
   FL_GUARD_BEGIN
   if (!layer) return FL_OK;
+  if (layer->join_open && hipStreamSynchronize(layer->stream) != hipSuccess) {   // the join that is still open
+    (void)hipGetLastError();
+    (void)hipDeviceSynchronize();
+  }
   release_tape(layer, true);  // the caller's stream may be gone by now
   if (layer->wt_fork_event) hipEventDestroy(layer->wt_fork_event);
   if (layer->wt_event) hipEventDestroy(layer->wt_event);

@@ -755,6 +755,30 @@ def test_allocation_trace_names_the_operator_of_every_buffer():
     assert open_ == {}
 
 
+@pytest.mark.parametrize("norm", ["pre", "post"])
+def test_backward_in_place_of_the_upstream_gradient(norm):
+    """dX may lie on dY: the weight gradients, which read dY at the end of the pass, see it unchanged."""
+    from paper_2201_12465_amd import binding as b
+    torch = torch_mod()
+    cfg = CONFIGS["cfg3_bert_base_bf16"].with_(B=3, T=40, norm=norm)
+    inp = make_inputs(cfg, seed=4, nontrivial=True)
+    p = {k: to_dev(v, cfg.dtype) for k, v in inp["params"].items()}
+    got = []
+    for in_place in (False, True):
+        layer = b.Layer(cfg.B, cfg.T, cfg.D, cfg.H, cfg.F, cfg.act, cfg.norm, cfg.dtype, cfg.eps)
+        g = {k: empty_dev(v.shape, cfg.dtype) for k, v in p.items()}
+        X, dY = to_dev(inp["X"], cfg.dtype), to_dev(inp["dY"], cfg.dtype)
+        Y = empty_dev(X.shape, cfg.dtype)
+        dX = dY if in_place else empty_dev(X.shape, cfg.dtype)
+        layer.forward(p, X, None, cfg.B, cfg.T, Y, stream_ptr())
+        layer.backward(p, dY, dX, g, stream_ptr())
+        torch.cuda.synchronize()
+        layer.destroy()
+        got.append([to_np(dX)] + [to_np(g[k]) for k in PARAM_NAMES])
+    for apart, here in zip(*got):
+        assert np.array_equal(apart, here)
+
+
 def test_error_paths():
     from paper_2201_12465_amd import binding as b
     cfg = CONFIGS["cfg1_tiny_f32"]
