@@ -786,9 +786,13 @@ hipError_t fwd_k(const void *qkv, const int32_t *lengths, const DropSpec &drop, 
 template <int DH, bool CAUSAL, bool DROP>
 hipError_t fwd_t(const void *qkv, const int32_t *lengths, const DropSpec &drop, int B, int T, int H, int dh, float scale,
                  void *o, float *lse, hipStream_t s) {
-  if constexpr (DH == 64 || DH == 192)
-    if (fwd_key_groups(DH, B, T, H) == 2) return fwd_k<DH, CAUSAL, DROP, 2>(qkv, lengths, drop, B, T, H, dh, scale, o, lse, s);
-  if constexpr (DH != 192) return fwd_k<DH, CAUSAL, DROP, 1>(qkv, lengths, drop, B, T, H, dh, scale, o, lse, s);
+  if constexpr (DH == 192) {
+    return fwd_k<DH, CAUSAL, DROP, 2>(qkv, lengths, drop, B, T, H, dh, scale, o, lse, s);
+  } else {
+    if constexpr (DH == 64)
+      if (fwd_key_groups(DH, B, T, H) == 2) return fwd_k<DH, CAUSAL, DROP, 2>(qkv, lengths, drop, B, T, H, dh, scale, o, lse, s);
+    return fwd_k<DH, CAUSAL, DROP, 1>(qkv, lengths, drop, B, T, H, dh, scale, o, lse, s);
+  }
 }
 
 template <int DH, int MODE, bool CAUSAL, bool DROP>
