@@ -54,8 +54,8 @@ __host__ __device__ constexpr int gemm_epi_kind(bool partial, int act, int dact,
          : (act == 0 && dact == 0 && !preact) ? EPI_PLAIN : EPI_LIGHT;
 }
 
-// PRE: the eight residual / aux values were already loaded by the caller (pre_res, pre_aux; bf16 only).
-template <typename T, bool DROP, bool PRE = false, int EPI = EPI_FULL>
+// PRE_RES / PRE_AUX: the eight residual / aux values were already loaded by the caller (pre_res, pre_aux; bf16 only).
+template <typename T, bool DROP, bool PRE_RES = false, bool PRE_AUX = false, int EPI = EPI_FULL>
 __device__ __forceinline__ void gemm_epilogue_oct(const GemmDev &p, int m, int n0, float (&v)[8],
                                                   const float (&bias8)[8], bf16x8_t pre_res = bf16x8_t{},
                                                   bf16x8_t pre_aux = bf16x8_t{}) {
@@ -83,7 +83,7 @@ __device__ __forceinline__ void gemm_epilogue_oct(const GemmDev &p, int m, int n
     for (int e = 0; e < 4; ++e) v[e] *= k0[e], v[e + 4] *= k1[e];
   }
   if (p.residual) {
-    if constexpr (PRE) {
+    if constexpr (PRE_RES) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) t[e] = static_cast<float>(pre_res[e]);
     } else {
@@ -93,7 +93,7 @@ __device__ __forceinline__ void gemm_epilogue_oct(const GemmDev &p, int m, int n
     for (int e = 0; e < 8; ++e) v[e] += t[e];
   }
   if (EPI != EPI_GELU_FWD && EPI != EPI_PLAIN && p.dact) {
-    if constexpr (PRE) {
+    if constexpr (PRE_AUX) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) t[e] = static_cast<float>(pre_aux[e]);
     } else {
@@ -130,8 +130,13 @@ __device__ __forceinline__ void gemm_staged_epilogue(const GemmDev &p, const f32
   constexpr int WC = TN * 32, CS = WC + 4;
   constexpr int LPR = WC / 8, RPP = 64 / LPR;  // lanes per row, rows per pass (lanes beyond LPR*RPP idle)
   constexpr int PASSES = (32 + RPP - 1) / RPP;
-  // bf16: 4 registers per prefetched oct; the large wavefront tiles have no registers to spare
-  constexpr bool PRE = sizeof(T) == 2 && TM * TN <= 4 && EPI != EPI_PARTIAL;
+  // Small wavefront tiles request both operands of every pass up front (bf16: 4 registers per oct), those of 160x32 outputs
+  // the one that the instance is for (12608 x 3072 x 768 with GELU': 113 -> 101 us).  Larger ones lose as much by the
+  // straight-line code as they gain (256x192, GELU' or ReLU').
+  constexpr bool SMALL = sizeof(T) == 2 && TM * TN <= 4 && EPI != EPI_PARTIAL, MEDIUM = sizeof(T) == 2 && TM * TN == 5;
+  constexpr bool PRE_AUX = SMALL ? EPI != EPI_PLAIN && EPI != EPI_GELU_FWD : MEDIUM && (EPI == EPI_GELU_BWD || EPI == EPI_LIGHT);
+  constexpr bool PRE_RES = SMALL || (MEDIUM && EPI == EPI_PLAIN);
+  constexpr bool PRE = PRE_RES || PRE_AUX;
   const int rl = lane / LPR, c8 = lane % LPR;
   const int n0 = nbase + c8 * 8;
   const bool lane_ok = rl < RPP && n0 < p.N;
@@ -140,9 +145,9 @@ __device__ __forceinline__ void gemm_staged_epilogue(const GemmDev &p, const f32
   // nothing left to overlap it at the end of the kernel.
   float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // a lane's eight columns are the same in every pass
   if (EPI != EPI_PARTIAL && p.bias && !p.partial && lane_ok) Oct<T>::load(static_cast<const T *>(p.bias) + n0, bias8);
-  bf16x8_t pre_res[PRE ? TM : 1][PRE ? PASSES : 1], pre_aux[PRE ? TM : 1][PRE ? PASSES : 1];
+  bf16x8_t pre_res[PRE_RES ? TM : 1][PRE_RES ? PASSES : 1], pre_aux[PRE_AUX ? TM : 1][PRE_AUX ? PASSES : 1];
   if constexpr (PRE) {
-    const bool has_res = p.residual && !p.partial, has_aux = EPI != EPI_PLAIN && EPI != EPI_GELU_FWD && p.dact && !p.partial;
+    const bool has_res = p.residual && !p.partial, has_aux = p.dact && !p.partial;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -150,10 +155,14 @@ __device__ __forceinline__ void gemm_staged_epilogue(const GemmDev &p, const f32
         const int r = rl + k * RPP, m = mbase + i * 32 + r;
         const bool ok = lane_ok && r < 32 && m < p.M;
         const size_t off = (size_t)m * p.ldc + n0;
-        pre_res[i][k] = bf16x8_t{};
-        pre_aux[i][k] = bf16x8_t{};
-        if (has_res && ok) pre_res[i][k] = *reinterpret_cast<const bf16x8_t *>(static_cast<const bf16_t *>(p.residual) + off);
-        if (has_aux && ok) pre_aux[i][k] = *reinterpret_cast<const bf16x8_t *>(static_cast<const bf16_t *>(p.aux) + off);
+        if constexpr (PRE_RES) {
+          pre_res[i][k] = bf16x8_t{};
+          if (has_res && ok) pre_res[i][k] = *reinterpret_cast<const bf16x8_t *>(static_cast<const bf16_t *>(p.residual) + off);
+        }
+        if constexpr (PRE_AUX) {
+          pre_aux[i][k] = bf16x8_t{};
+          if (has_aux && ok) pre_aux[i][k] = *reinterpret_cast<const bf16x8_t *>(static_cast<const bf16_t *>(p.aux) + off);
+        }
       }
   }
 #pragma unroll
@@ -174,8 +183,8 @@ __device__ __forceinline__ void gemm_staged_epilogue(const GemmDev &p, const f32
         const float4 lo = *reinterpret_cast<const float4 *>(cw + r * CS + c8 * 8);
         const float4 hi = *reinterpret_cast<const float4 *>(cw + r * CS + c8 * 8 + 4);
         float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-        if constexpr (PRE) gemm_epilogue_oct<T, DROP, true, EPI>(p, m, n0, v, bias8, pre_res[i][k], pre_aux[i][k]);
-        else gemm_epilogue_oct<T, DROP, false, EPI>(p, m, n0, v, bias8);
+        gemm_epilogue_oct<T, DROP, PRE_RES, PRE_AUX, EPI>(p, m, n0, v, bias8, pre_res[PRE_RES ? i : 0][PRE_RES ? k : 0],
+                                                          pre_aux[PRE_AUX ? i : 0][PRE_AUX ? k : 0]);
       }
     }
   }

@@ -240,7 +240,7 @@ __device__ __forceinline__ void gemm_small_tile(const GemmDev &p, int row0, int 
         v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
         v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
       }
-      gemm_epilogue_oct<T, DROP, PRE, EPI>(p, m, n0, v, bias8[o], pre_res[o], pre_aux[o]);
+      gemm_epilogue_oct<T, DROP, PRE, PRE, EPI>(p, m, n0, v, bias8[o], pre_res[o], pre_aux[o]);
     }
   }
 }
