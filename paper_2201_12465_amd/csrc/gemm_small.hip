@@ -72,7 +72,7 @@ hipError_t launch_v(const GemmArgs &a, const GemmDev &d, int splits, int v, hipS
 //   several); the 128x128 tiles of gemm_pipe.hip: 4.6 us plus 69 KB/us.  24 x 768 x 3072: 26.8 -> 5.7; 744 x 768 x
 //   3072: 28.3 -> 13.0; 1001 x 2048 x 512: 8.9 -> 7.2.
 //   fp32: a fixed part plus the matrix cores' time for the fullest CU's tiles, 5-7.5 ns per k and 32x32 block (the
-//   64 x 64 tiles reuse fragments: 4.1).  1024 x 256 x 1024: 12.4 -> 8.9; 2048 x 512 x 2048: 51 -> 39.
+//   64 x 64 tiles reuse fragments: 4.1, 6.1 where a CU gets several).  1024 x 256 x 1024: 12.4 -> 8.9; 2048 x 512 x 2048: 51 -> 39.
 int gemm_small_pick(int dt, bool a_kc, int M, int N, int K, bool pipe_eligible, bool gelu) {
   if (!a_kc) return -1;
   const int rows[3] = {64, 96, 128};
@@ -84,7 +84,7 @@ int gemm_small_pick(int dt, bool a_kc, int M, int N, int K, bool pipe_eligible, 
     const double n = (double)((tiles[v] + 255) / 256);   // tiles of the fullest CU
     double us;
     if (dt == DT_F32) {
-      const double fix[3] = {3.5, 3.5, 4.8}, one[3] = {0.0057, 0.010, 0.0164}, more[3] = {0.0075, 0.0125, 0.0164};
+      const double fix[3] = {3.5, 3.5, 4.8}, one[3] = {0.0057, 0.010, 0.0164}, more[3] = {0.0075, 0.0125, 0.0245};
       us = fix[v] + n * K * (n > 1 ? more[v] : one[v]);
     } else {
       const double fix[3] = {2.6, 3.0, 4.0}, rate = v == 0 && n > 1 ? 50e3 : 85e3;
